@@ -55,6 +55,37 @@ def test_forward_and_gradient_match_oracle(W, n, J):
         pos += k
 
 
+@pytest.mark.parametrize("n,J,B", [(8, 2, 1), (16, 1, 5), (32, 4, 2), (64, 1, 1), (128, 2, 3)])
+def test_network_tiles_match_oracle(W, n, J, B):
+    """Stacks of every kind of tile: sides 2 to 8 (tiles that cover the image
+    several times), 16 (one 16 x 16 tile), 32 (rows as wide as a tile) and 64 (two
+    tiles side by side), with one or three channels and few images.  A float32
+    sum of at most 3 x 288 products is off by less than 900 x 2^-24 of the sum of
+    their magnitudes; the bars are those of the test above."""
+    net = W.Cnn(n, J, 32, seed=5)
+    rng = np.random.default_rng(n + J)
+    p = (rng.standard_normal(net.nparam) * 0.05).astype(np.float32)
+    net.set_params(p)
+    pr = net.get_params(rounded=True).astype(np.float64)
+    x0 = rng.standard_normal((B, n * n)).astype(np.float32)
+    tgt = rng.standard_normal((B, n * n)).astype(np.float32)
+    pred = net.predict(dev(x0).reshape(-1)).cpu().numpy().reshape(B, -1)
+    pred_o = ocnn.forward(pr, x0.astype(np.float64), n, J, 32)
+    assert np.max(np.abs(pred - pred_o)) <= 1e-5 * np.max(np.abs(pred_o))
+    loss, g = net.loss_grad(dev(x0).reshape(-1), dev(tgt).reshape(-1))
+    loss_o, g_o = ocnn.loss_and_grad(pr, x0.astype(np.float64), tgt.astype(np.float64), n, J, 32)
+    assert abs(loss - loss_o) <= 1e-6 * loss_o
+    scale, pos = np.max(np.abs(g_o)), 0
+    for shp in ocnn.param_shapes(n, J, 32):
+        k = int(np.prod(shp))
+        assert np.max(np.abs(g[pos:pos + k] - g_o[pos:pos + k])) <= 1e-4 * scale
+        assert np.linalg.norm(g[pos:pos + k] - g_o[pos:pos + k]) <= 1e-4 * max(np.linalg.norm(g_o[pos:pos + k]),
+                                                                              1e-3 * scale)
+        pos += k
+    again, g2 = net.loss_grad(dev(x0).reshape(-1), dev(tgt).reshape(-1))
+    assert again == loss and np.array_equal(g, g2)   # every sum has a fixed order
+
+
 def test_adam_step_matches_closed_form(W):
     n, J, F = 32, 2, 32
     net = W.Cnn(n, J, F, seed=6)
