@@ -217,7 +217,7 @@ void apply_Ht(const wdb_exact* ex, const TI* in, TO* out, hipStream_t s) {
 
 // g = Psi^* H^* (H Psi v - u0); leaves H Psi v - u0 in ex->r.
 void gradient(wdb_exact* ex, const Filter& f, const float* v, float* g, hipStream_t s) {
-  dwt_inverse(ex->n, ex->levels, f, v, ex->img.p, ex->sa.p, ex->sb.p, s);
+  dwt_inverse(ex->n, ex->levels, f, v, ex->img.p, s);
   apply_H(ex, ex->img.p, ex->u0.p, ex->r.p, s);
   apply_Ht(ex, ex->r.p, ex->gimg.p, s);
   dwt_forward(ex->n, ex->levels, f, ex->gimg.p, g, ex->sa.p, ex->sb.p, s);

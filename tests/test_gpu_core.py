@@ -86,6 +86,40 @@ def test_dwt_batched_matches_single(W, name, n, J, count):
         assert np.max(np.abs(v[i] - u[i])) <= 2e-6
 
 
+@pytest.mark.parametrize("name,n,J", [("haar", 2, 1), ("haar", 4, 2), ("db4", 8, 1), ("sym6", 16, 1), ("db4", 256, 1),
+                                      ("db4", 256, 4), ("sym6", 256, 2), ("sym6", 512, 4), ("db4", 512, 2),
+                                      ("db4", 1024, 6), ("haar", 1024, 3), ("haar", 2048, 9), ("db4", 2048, 4)])
+def test_dwt_launch_plans_match_oracle(W, name, n, J):
+    """Every way the transform is split: one block per image (sides up to 128),
+    one to three levels per launch before it or alone, a second launch of many
+    blocks (side 2048), 32 x 32 and 64 x 64 pixels per inverse block; the inverse
+    also into a buffer that is only 4-byte aligned.  Bars of the tests above."""
+    print(f"dwt plan {name} n={n} J={J}", flush=True)
+    u = np.random.default_rng(n + J).random((n, n)).astype(np.float32)
+    x = host(W.dwt(dev(u).reshape(-1), name, J))
+    xo = dwt.dwt2(u.astype(np.float64), filters.by_name(name), J)
+    assert np.max(np.abs(x - xo)) <= 2e-6 * np.max(np.abs(xo))
+    c = np.random.default_rng(1).standard_normal(n * n).astype(np.float32)
+    odd = torch.zeros(n * n + 1, device="cuda")[1:]
+    v = host(W.dwt(dev(c), name, J, inverse=True, out=odd))
+    vo = dwt.idwt2(c.astype(np.float64), filters.by_name(name), J, n).ravel()
+    assert np.max(np.abs(v - vo)) <= 2e-6 * np.max(np.abs(vo))
+    assert np.array_equal(v, host(W.dwt(dev(c), name, J, inverse=True)))
+
+
+def test_dwt_many_images_match_single(W):
+    """More images than a launch takes, and enough blocks for the larger tile."""
+    n, J, count = 64, 2, 261
+    u = np.random.default_rng(7).random((count, n * n)).astype(np.float32)
+    x = W.dwt_batched(dev(u), "db4", J)
+    v = host(W.dwt_batched(x, "db4", J, inverse=True))
+    x = host(x)
+    for i in (0, 31, 32, 100, 260):
+        assert np.array_equal(x[i], host(W.dwt(dev(u[i]), "db4", J)))
+        assert np.array_equal(v[i], host(W.dwt(dev(x[i]), "db4", J, inverse=True)))
+    assert np.max(np.abs(v - u)) <= 2e-6
+
+
 @pytest.mark.parametrize("field", [synth.psf_isotropic(64, 1.0, 3.0), synth.psf_rotating(128, 4.0, 1.0),
                                    synth.psf_rotating(32, 2.5, 0.7)])
 def test_blur_matches_oracle(W, field):
