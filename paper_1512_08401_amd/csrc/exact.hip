@@ -7,16 +7,26 @@
 //
 // For a spatially varying PSF there is no fast exact H (the paper's FFT
 // applies to convolutions only), so both products evaluate the truncated
-// PSFs on the fly from the field: H u gathers, for each target pixel, the
-// sources whose ellipse can reach it (a box bounded per 16 x 16 tile); H^* r
-// sums, for each source, r over its own ellipse's bounding box.  The PSF
-// weights are computed in float64 with the formula of psf.hpp (the same
-// cut-off decisions as the field's blur), accumulated in float64; images
-// and coefficients are float32.  Because Psi is orthogonal, Psi^* H Psi is
-// the untruncated Theta, so this solves the problem before thresholding.
+// PSFs on the fly, in float64 with the field's own cut-off decisions,
+// accumulating in float64; images and coefficients are float32.  Because Psi
+// is orthogonal, Psi^* H Psi is the untruncated Theta, so this solves the
+// problem before thresholding.
+//
+// The products are bound by the float64 arithmetic of the weights.  So a
+// weight costs as little as it can: per source the handle keeps the rotated
+// axes divided by the sigmas (q is then two products and four fused sums
+// instead of two divisions) and 1 / Z; per 16 x 16 tile of sources and row
+// offset it keeps the interval of column offsets any of them reaches (at sigma 4
+// and 1, 150 of the 625 offsets of the box); and a block stages its
+// neighbourhood in LDS.  Where q is so near the cut-off that its rounding could
+// decide, the decision is taken again with the field's own formula.
+// 512 x 512, sigma 4 and 1: H 302 -> 60 us, H^* 203 -> 27 us (its H^* needs half of
+// the weights); about 30 instructions per weight, 3 of 4 issue slots used.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <functional>
+#include <type_traits>
 #include <vector>
 
 #include "common.hpp"
@@ -28,9 +38,10 @@ struct wdb_exact {
   int32_t n = 0, levels = 0, wavelet = 0;
   int64_t N = 0;
   wdb::PsfField F;
-  wdb::DevBuf<int2> box;      // per source: half-widths (hx, hy) of its ellipse's bounding box
-  wdb::DevBuf<int2> tbox;     // per 16 x 16 tile of sources: the largest half-widths
+  wdb::DevBuf<double> coef;   // per source, in planes: (c / a, s / a, c / b, s / b) kScale, 1 / Z
+  wdb::DevBuf<short2> reach;  // per 16 x 16 tile of sources and dy: the dx any of them reaches
   int ntile = 0;              // tiles per side
+  double near = 0.0;          // q is within this of the formula's value
   bool has_L = false;
   double L = 0.0;
   // workspace
@@ -42,98 +53,240 @@ struct wdb_exact {
 namespace wdb {
 namespace {
 
-constexpr int kT = 16;        // tile side of the products
-constexpr int kThreads = kT * kT;
+constexpr int kT = 16;        // side of the tiles whose reach is kept
 
-// Bounding box of source s's truncated ellipse: |dx| <= trunc sqrt(a^2 c^2 + b^2 s^2),
-// |dy| <= trunc sqrt(a^2 s^2 + b^2 c^2); one more pixel of margin (the
-// weight test itself decides), at most the field radius.
-__global__ __launch_bounds__(256) void k_exact_box(PsfDev P, int2* __restrict__ box) {
+// The coefficients hold q scaled by log2(e) / 2, so that the weight is 2^-q.
+constexpr double kScale = 0.8493218002880191;   // sqrt(log2(e) / 2)
+
+// Device view of the handle's precomputed field.
+struct ExDev {
+  PsfDev P;
+  const double* coef;
+  const short2* reach;   // [tile][2 R + 1], dy = -R .. R; lo > hi: nothing
+  int ntile;
+  double sure, never;    // q <= sure is inside, q > never outside
+};
+
+__global__ __launch_bounds__(256) void k_exact_coef(PsfDev P, double* __restrict__ coef) {
   const int64_t s = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   const int64_t N = static_cast<int64_t>(P.n) * P.n;
   if (s >= N) return;
   const double a = P.sM[s], b = P.sm[s], c = P.c[s], sn = P.s[s];
-  const int hx = static_cast<int>(floor(P.trunc * sqrt(a * a * c * c + b * b * sn * sn))) + 1;
-  const int hy = static_cast<int>(floor(P.trunc * sqrt(a * a * sn * sn + b * b * c * c))) + 1;
-  box[s] = make_int2(min(hx, P.R), min(hy, P.R));
+  coef[s] = kScale * c / a;
+  coef[N + s] = kScale * sn / a;
+  coef[2 * N + s] = kScale * c / b;
+  coef[3 * N + s] = kScale * sn / b;
+  coef[4 * N + s] = 1.0 / P.Z[s];
 }
 
-// Largest half-widths over each tile of sources.
-__global__ __launch_bounds__(256) void k_exact_tbox(const int2* __restrict__ box, int n, int ntile,
-                                                    int2* __restrict__ tbox) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= ntile * ntile) return;
-  const int tr = t / ntile, tc = t % ntile;
-  int hx = 0, hy = 0;
-  for (int r = tr * kT; r < min(n, (tr + 1) * kT); ++r)
-    for (int c = tc * kT; c < min(n, (tc + 1) * kT); ++c) {
-      const int2 b = box[static_cast<int64_t>(r) * n + c];
-      hx = max(hx, b.x);
-      hy = max(hy, b.y);
+// Reach of a tile of sources (blockIdx.x), thread = source.
+__global__ __launch_bounds__(kT * kT) void k_exact_reach(PsfDev P, int ntile, short2* __restrict__ reach) {
+  __shared__ int lo, hi;
+  const int r = static_cast<int>(blockIdx.x) / ntile * kT + static_cast<int>(threadIdx.x) / kT;
+  const int c = static_cast<int>(blockIdx.x) % ntile * kT + static_cast<int>(threadIdx.x) % kT;
+  const bool on = r < P.n && c < P.n;
+  const int64_t s = on ? static_cast<int64_t>(r) * P.n + c : 0;
+  const double a = P.sM[s], b = P.sm[s], cs = P.c[s], sn = P.s[s];
+  // the ellipse's bounding box and one more pixel; the formula decides
+  const int hx = min(static_cast<int>(floor(P.trunc * sqrt(a * a * cs * cs + b * b * sn * sn))) + 1, P.R);
+  const int hy = min(static_cast<int>(floor(P.trunc * sqrt(a * a * sn * sn + b * b * cs * cs))) + 1, P.R);
+  for (int dy = -P.R; dy <= P.R; ++dy) {
+    if (threadIdx.x == 0) {
+      lo = P.R + 1;
+      hi = -P.R - 1;
     }
-  tbox[t] = make_int2(hx, hy);
-}
-
-// out[i] = sum over sources s of k_s(i - s) in[s]  (- sub[i]): for the target
-// tile of this block, the offsets searched are bounded by the largest boxes
-// of the source tiles within the field radius.
-template <typename TI, typename TO>
-__global__ __launch_bounds__(kThreads) void k_exact_fwd(PsfDev P, const int2* __restrict__ tbox, int ntile,
-                                                        const TI* __restrict__ in, const float* __restrict__ sub,
-                                                        TO* __restrict__ out) {
-  __shared__ int2 hb;
-  const int n = P.n;
-  const int tr = blockIdx.y, tc = blockIdx.x;
-  if (threadIdx.x == 0) {
-    const int reach = P.R / kT + 1;
-    int hx = 0, hy = 0;
-    for (int dr = -reach; dr <= reach; ++dr)
-      for (int dc = -reach; dc <= reach; ++dc) {
-        const int2 b = tbox[((tr + dr + ntile) % ntile) * ntile + (tc + dc + ntile) % ntile];
-        hx = max(hx, b.x);
-        hy = max(hy, b.y);
+    __syncthreads();
+    if (on && dy >= -hy && dy <= hy) {
+      int first = -hx, last = hx;
+      while (first <= hx && psf_q(P, s, dy, first) > P.T2) ++first;
+      while (last >= first && psf_q(P, s, dy, last) > P.T2) --last;
+      if (first <= last) {
+        atomicMin(&lo, first);
+        atomicMax(&hi, last);
       }
-    hb = make_int2(hx, hy);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+      reach[static_cast<int64_t>(blockIdx.x) * (2 * P.R + 1) + dy + P.R] = make_short2(static_cast<short>(lo),
+                                                                                      static_cast<short>(hi));
+    __syncthreads();
   }
+}
+
+// a b + c with c from scalar registers.  (The compiler would copy each constant
+// into the accumulator of a two-address v_fmac: a third more instructions here.)
+__device__ __forceinline__ double fma_const(double a, double b, double c) {
+  double d;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+  return d;
+}
+
+// 2^-x for x >= 0: -x = n + r, |r| <= 1/2, and the Taylor polynomial of degree
+// 13 of 2^r (its remainder is below 5e-18) times 2^n.  n comes from the low bits
+// of a sum with 1.5 * 2^52.
+__device__ __forceinline__ double exp2_neg(double x) {
+  constexpr double kShift = 6755399441055744.0, kLn2 = 0.6931471805599453;
+  const double t = kShift - x;
+  const double r = (kShift - t) - x;
+  double c[14] = {1.0};
+#pragma unroll
+  for (int k = 1; k < 14; ++k) c[k] = c[k - 1] * kLn2 / k;
+  double p = c[13];
+#pragma unroll
+  for (int k = 12; k > 0; --k) p = fma_const(p, r, c[k]);
+  return ldexp(fma(p, r, 1.0), __double2loint(t));
+}
+
+// acc + w v, with w the weight (before 1 / Z) of source s, coefficients k, at
+// offset (dy, dx); acc past the cut-off.
+__device__ __forceinline__ double weigh(const ExDev& E, int64_t s, double k0, double k1, double k2, double k3,
+                                        int dy, int dx, double fy, double fx, double v, double acc) {
+  const double u1 = fma(fx, k0, fy * k1), u2 = fma(-fx, k3, fy * k2);
+  const double q = fma(u1, u1, u2 * u2);
+  const bool maybe = q <= E.never;
+  if (!__any(maybe)) return acc;
+  bool in = q <= E.sure;
+  if (maybe && !in) in = psf_q(E.P, s, dy, dx) <= E.P.T2;
+  const double sum = fma(exp2_neg(q), v, acc);
+  return in ? sum : acc;
+}
+
+// Interval of dx that any source of the tiles covering rows [r0, r1] and columns
+// [c0, c1] (any integers, periodic) reaches at dy.
+__device__ __forceinline__ int2 reach_of(const ExDev& E, int r0, int r1, int c0, int c1, int dy) {
+  const int rows = min((r1 >> 4) - (r0 >> 4) + 1, E.ntile), cols = min((c1 >> 4) - (c0 >> 4) + 1, E.ntile);
+  int lo = E.P.R + 1, hi = -E.P.R - 1;
+  for (int i = 0; i < rows; ++i)
+    for (int j = 0; j < cols; ++j) {
+      const int tr = ((r0 >> 4) + i) & (E.ntile - 1), tc = ((c0 >> 4) + j) & (E.ntile - 1);
+      const short2 v = E.reach[static_cast<int64_t>(tr * E.ntile + tc) * (2 * E.P.R + 1) + dy + E.P.R];
+      lo = min(lo, static_cast<int>(v.x));
+      hi = max(hi, static_cast<int>(v.y));
+    }
+  return make_int2(lo, hi);
+}
+
+struct Source {
+  double k[4], v;   // coefficients, in / Z
+};
+
+__device__ __forceinline__ Source source(const ExDev& E, int64_t N, int64_t s, double in) {
+  return Source{{E.coef[s], E.coef[N + s], E.coef[2 * N + s], E.coef[3 * N + s]}, E.coef[4 * N + s] * in};
+}
+
+// A product's block: kTW x TH targets (sources for H^*), each summed by
+// kThreads / (kTW TH) threads over the row offsets dealt to them in turn.
+constexpr int kTW = 32, kThreads = 1024;
+
+// The targets' sums from their threads' (red: kThreads float64 of LDS), thread < kTW TH.
+template <int TH>
+__device__ __forceinline__ double sum_groups(double* red, double acc) {
+  if (TH == 32) return acc;
   __syncthreads();
-  const int ir = tr * kT + static_cast<int>(threadIdx.x) / kT;
-  const int ic = tc * kT + static_cast<int>(threadIdx.x) % kT;
-  if (ir >= n || ic >= n) return;
-  const int hx = hb.x, hy = hb.y;
+  red[threadIdx.x] = acc;
+  __syncthreads();
+  if (threadIdx.x < kTW * TH)
+    for (int k = threadIdx.x + kTW * TH; k < kThreads; k += kTW * TH) acc += red[k];
+  return acc;
+}
+
+// H: out[i] = sum over sources s of k_s(i - s) in[s]  (- sub[i]).  `rows` row
+// offsets at a time have their sources staged in LDS (40 bytes each: neighbouring
+// sources are on different banks); rows = 0: straight from memory.
+template <typename TI, typename TO, int TH>
+__global__ __launch_bounds__(kThreads) void k_exact_fwd(ExDev E, int rows, const TI* __restrict__ in,
+                                                        const float* __restrict__ sub, TO* __restrict__ out) {
+  extern __shared__ __align__(16) double lds[];
+  const int n = E.P.n, R = E.P.R, m = n - 1, span = 2 * R + 1;
+  const int64_t N = static_cast<int64_t>(n) * n;
+  const int y0 = blockIdx.y * TH, x0 = blockIdx.x * kTW, W = kTW + 2 * R;
+  int2* rng = reinterpret_cast<int2*>(lds + kThreads);
+  Source* src = reinterpret_cast<Source*>(rng + span);
+  for (int k = threadIdx.x; k < span; k += kThreads) {
+    const int dy = k - R;
+    rng[k] = reach_of(E, y0 - dy, y0 + TH - 1 - dy, x0 - R, x0 + kTW - 1 + R, dy);
+  }
+  const int id = static_cast<int>(threadIdx.x) % (kTW * TH), group = static_cast<int>(threadIdx.x) / (kTW * TH);
+  const int ty = id / kTW, tx = id % kTW;
   double acc = 0.0;
-  for (int dy = -hy; dy <= hy; ++dy) {
-    const int sr = (ir - dy + n) & (n - 1);
-    for (int dx = -hx; dx <= hx; ++dx) {
-      const int sc = (ic - dx + n) & (n - 1);
-      const int64_t s = static_cast<int64_t>(sr) * n + sc;
-      const double w = psf_unnormalised(P, s, dy, dx);
-      if (w != 0.0) acc += (w / P.Z[s]) * static_cast<double>(in[s]);
+  for (int d0 = -R; d0 <= R; d0 += rows ? rows : span) {
+    const int d1 = rows ? min(d0 + rows - 1, R) : R;   // offsets d0 .. d1: source rows y0 - d1 .. y0 + TH - 1 - d0
+    __syncthreads();
+    if (rows)
+      for (int e = threadIdx.x; e < W * (TH + d1 - d0); e += kThreads) {
+        const int r = e / W, c = e - r * W;
+        const int64_t s = static_cast<int64_t>((y0 - d1 + r) & m) * n + ((x0 - R + c) & m);
+        src[e] = source(E, N, s, static_cast<double>(in[s]));
+      }
+    __syncthreads();
+    for (int dy = d0 + group; dy <= d1; dy += kThreads / (kTW * TH)) {
+      const int2 d = rng[dy + R];
+      const int lo = __builtin_amdgcn_readfirstlane(d.x), hi = __builtin_amdgcn_readfirstlane(d.y);
+      const double fy = static_cast<double>(dy);
+      const int64_t row = static_cast<int64_t>((y0 + ty - dy) & m) * n;
+      double fx = static_cast<double>(lo);
+      if (rows) {
+        const Source* p = src + (ty + d1 - dy) * W + tx + R - lo;
+        for (int dx = lo; dx <= hi; ++dx, --p, fx += 1.0)
+          acc = weigh(E, row + ((x0 + tx - dx) & m), p->k[0], p->k[1], p->k[2], p->k[3], dy, dx, fy, fx, p->v, acc);
+      } else {
+        for (int dx = lo; dx <= hi; ++dx, fx += 1.0) {
+          const int64_t s = row + ((x0 + tx - dx) & m);
+          const Source q = source(E, N, s, static_cast<double>(in[s]));
+          acc = weigh(E, s, q.k[0], q.k[1], q.k[2], q.k[3], dy, dx, fy, fx, q.v, acc);
+        }
+      }
     }
   }
-  const int64_t i = static_cast<int64_t>(ir) * n + ic;
+  acc = sum_groups<TH>(lds, acc);
+  if (group || y0 + ty >= n || x0 + tx >= n) return;
+  const int64_t i = static_cast<int64_t>(y0 + ty) * n + x0 + tx;
   out[i] = static_cast<TO>(sub ? acc - static_cast<double>(sub[i]) : acc);
 }
 
-// out[s] = sum_d k_s(d) in[s + d]  (H^*), over the source's own box.
-template <typename TI, typename TO>
-__global__ __launch_bounds__(256) void k_exact_adj(PsfDev P, const int2* __restrict__ box,
-                                                   const TI* __restrict__ in, TO* __restrict__ out) {
-  const int64_t s = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int n = P.n;
+// H^*: out[s] = sum_d k_s(d) in[s + d].  With STAGE the image within the field's
+// radius is staged in LDS.  A PSF is even in d, also in its roundings, so half of
+// the offsets are enough (47 -> 27 us).
+template <typename TI, typename TO, int TH, bool STAGE>
+__global__ __launch_bounds__(kThreads) void k_exact_adj(ExDev E, const TI* __restrict__ in, TO* __restrict__ out) {
+  extern __shared__ __align__(16) double lds[];
+  const int n = E.P.n, R = E.P.R, m = n - 1;
   const int64_t N = static_cast<int64_t>(n) * n;
-  if (s >= N) return;
-  const int sr = static_cast<int>(s / n), sc = static_cast<int>(s % n);
-  const int2 b = box[s];
-  const double iz = 1.0 / P.Z[s];
+  const int y0 = blockIdx.y * TH, x0 = blockIdx.x * kTW, W = kTW + 2 * R;
+  int2* rng = reinterpret_cast<int2*>(lds + kThreads);   // dy = 0 .. R
+  double* img = reinterpret_cast<double*>(rng + R + 1);
+  for (int k = threadIdx.x; k <= R; k += kThreads) rng[k] = reach_of(E, y0, y0 + TH - 1, x0, x0 + kTW - 1, k);
+  if (STAGE)
+    for (int e = threadIdx.x; e < W * (TH + 2 * R); e += kThreads) {
+      const int r = e / W, c = e - r * W;
+      img[e] = static_cast<double>(in[static_cast<int64_t>((y0 - R + r) & m) * n + ((x0 - R + c) & m)]);
+    }
+  __syncthreads();
+  const int id = static_cast<int>(threadIdx.x) % (kTW * TH), group = static_cast<int>(threadIdx.x) / (kTW * TH);
+  const int ty = id / kTW, tx = id % kTW;
+  const int64_t s = static_cast<int64_t>((y0 + ty) & m) * n + ((x0 + tx) & m);
+  const Source src = source(E, N, s, 1.0);
+  const auto at = [&](int dy, int dx) {
+    return static_cast<double>(in[static_cast<int64_t>((y0 + ty + dy) & m) * n + ((x0 + tx + dx) & m)]);
+  };
+  const double* mid = img + (ty + R) * W + tx + R;
   double acc = 0.0;
-  for (int dy = -b.y; dy <= b.y; ++dy) {
-    const int64_t row = static_cast<int64_t>((sr + dy + n) & (n - 1)) * n;
-    for (int dx = -b.x; dx <= b.x; ++dx) {
-      const double w = psf_unnormalised(P, s, dy, dx);
-      if (w != 0.0) acc += w * static_cast<double>(in[row + ((sc + dx + n) & (n - 1))]);
+  if (group == 0)
+    acc = weigh(E, s, src.k[0], src.k[1], src.k[2], src.k[3], 0, 0, 0.0, 0.0, STAGE ? *mid : at(0, 0), acc);
+  for (int dy = group; dy <= R; dy += kThreads / (kTW * TH)) {
+    const int2 d = rng[dy];
+    const int lo = dy ? __builtin_amdgcn_readfirstlane(d.x) : 1, hi = __builtin_amdgcn_readfirstlane(d.y);
+    const double fy = static_cast<double>(dy);
+    const double *p = mid + dy * W + lo, *q = mid - dy * W - lo;
+    double fx = static_cast<double>(lo);
+    for (int dx = lo; dx <= hi; ++dx, ++p, --q, fx += 1.0) {
+      const double v = STAGE ? *p + *q : at(dy, dx) + at(-dy, -dx);
+      acc = weigh(E, s, src.k[0], src.k[1], src.k[2], src.k[3], dy, dx, fy, fx, v, acc);
     }
   }
-  out[s] = static_cast<TO>(acc * iz);
+  acc = sum_groups<TH>(lds, acc);
+  if (group || y0 + ty >= n || x0 + tx >= n) return;
+  out[s] = static_cast<TO>(acc * src.v);
 }
 
 // Proximal step and momentum of Alg. 1 (beta from the host: the iteration
@@ -201,18 +354,84 @@ __global__ void k_exact_init(const float* __restrict__ src, float* __restrict__ 
   y[i] = v;
 }
 
-dim3 tile_grid(const wdb_exact* ex) { return dim3(ex->ntile, ex->ntile); }
 dim3 pix_grid(int64_t N) { return dim3(static_cast<unsigned>((N + 255) / 256)); }
+
+ExDev view(const wdb_exact* ex) {
+  const double T2 = ex->F.trunc * ex->F.trunc;
+  const double k2 = kScale * kScale;
+  return ExDev{ex->F.dev(), ex->coef.p, ex->reach.p, ex->ntile, k2 * (T2 - ex->near), k2 * (T2 + ex->near)};
+}
+
+// f(TH): 32 x 32 targets per block where those fill the chip, else 32 x 8 with four
+// threads per target, else 32 x 2 with sixteen.  Always 16 waves a block: one wave
+// of 32 x 2 alone is a serial chain (side 256, sigma 4 and 1: H 41 -> 22 us with
+// four threads per target; side 128: 54 -> 12 us with sixteen).
+template <typename F>
+void with_tile(int n, F&& f) {
+  using std::integral_constant;
+  if (n >= 512)
+    f(integral_constant<int, 32>{});
+  else if (n >= 256)
+    f(integral_constant<int, 8>{});
+  else
+    f(integral_constant<int, 2>{});
+}
+
+dim3 grid_of(int n, int TH) { return dim3((n + kTW - 1) / kTW, (n + TH - 1) / TH); }
+
+constexpr size_t kLds = 160 * 1024;
+
+// More than 64 KiB of LDS needs the kernel's limit raised, once per device (`done`: a bit per device).
+void raise_lds(const void* kernel, int device, std::atomic<uint64_t>& done) {
+  const uint64_t bit = uint64_t{1} << (device & 63);
+  if (done.load() & bit) return;
+  WDB_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLds));
+  done.fetch_or(bit);
+}
+
+// Row offsets of H staged at a time: all where the LDS holds their sources, else
+// as many as it holds (512 x 512, sigma 6 and 1, two parts: 112 us, straight from
+// memory 243 us), unless each source row would then serve few offsets.
+int staged_rows(int R, int TH) {
+  const size_t row = sizeof(Source) * (kTW + 2 * R);
+  const size_t room = kLds - kThreads * sizeof(double) - (2 * static_cast<size_t>(R) + 1) * sizeof(int2);
+  const int fit = static_cast<int>(room / row) - TH + 1, groups = kThreads / (kTW * TH);
+  if (fit >= 2 * R + 1) return 2 * R + 1;
+  return fit >= 8 ? std::max(fit / groups, 1) * groups : 0;
+}
 
 template <typename TI, typename TO>
 void apply_H(const wdb_exact* ex, const TI* in, const float* sub, TO* out, hipStream_t s) {
-  hipLaunchKernelGGL((k_exact_fwd<TI, TO>), tile_grid(ex), dim3(kThreads), 0, s, ex->F.dev(), ex->tbox.p,
-                     ex->ntile, in, sub, out);
+  with_tile(ex->n, [&](auto Hc) {
+    constexpr int TH = decltype(Hc)::value;
+    const int R = ex->F.R, rows = std::min(staged_rows(R, TH), 2 * R + 1);
+    const size_t bytes = kThreads * sizeof(double) + (2 * static_cast<size_t>(R) + 1) * sizeof(int2) +
+                         (rows ? sizeof(Source) * (kTW + 2 * R) * (TH + rows - 1) : 0);
+    static std::atomic<uint64_t> done{0};
+    raise_lds(reinterpret_cast<const void*>(k_exact_fwd<TI, TO, TH>), ex->device, done);
+    hipLaunchKernelGGL((k_exact_fwd<TI, TO, TH>), grid_of(ex->n, TH), dim3(kThreads), bytes, s, view(ex), rows, in,
+                       sub, out);
+  });
 }
 
 template <typename TI, typename TO>
 void apply_Ht(const wdb_exact* ex, const TI* in, TO* out, hipStream_t s) {
-  hipLaunchKernelGGL((k_exact_adj<TI, TO>), pix_grid(ex->N), dim3(256), 0, s, ex->F.dev(), ex->box.p, in, out);
+  with_tile(ex->n, [&](auto Hc) {
+    constexpr int TH = decltype(Hc)::value;
+    const size_t R = ex->F.R, fixed = kThreads * sizeof(double) + (R + 1) * sizeof(int2);
+    const size_t all = fixed + sizeof(double) * (kTW + 2 * R) * (TH + 2 * R);
+    const auto go = [&](auto Sc, size_t bytes) {
+      constexpr bool ST = decltype(Sc)::value;
+      static std::atomic<uint64_t> done{0};
+      raise_lds(reinterpret_cast<const void*>(k_exact_adj<TI, TO, TH, ST>), ex->device, done);
+      hipLaunchKernelGGL((k_exact_adj<TI, TO, TH, ST>), grid_of(ex->n, TH), dim3(kThreads), bytes, s, view(ex), in,
+                         out);
+    };
+    if (all <= kLds)
+      go(std::true_type{}, all);
+    else
+      go(std::false_type{}, fixed);
+  });
 }
 
 // g = Psi^* H^* (H Psi v - u0); leaves H Psi v - u0 in ex->r.
@@ -276,12 +495,17 @@ wdb_status wdb_exact_create(const wdb_psf_field* field, int32_t wavelet, int32_t
     ex->N = static_cast<int64_t>(field->n) * field->n;
     ex->F.upload(field, s);
     const int64_t N = ex->N;
-    ex->box.alloc(N);
     ex->ntile = (ex->n + wdb::kT - 1) / wdb::kT;
-    ex->tbox.alloc(static_cast<size_t>(ex->ntile) * ex->ntile);
-    hipLaunchKernelGGL(wdb::k_exact_box, wdb::pix_grid(N), dim3(256), 0, s, ex->F.dev(), ex->box.p);
-    hipLaunchKernelGGL(wdb::k_exact_tbox, dim3((ex->ntile * ex->ntile + 255) / 256), dim3(256), 0, s, ex->box.p,
-                       ex->n, ex->ntile, ex->tbox.p);
+    WDB_REQUIRE(ex->F.R < 32767, WDB_ERR_SIZE, "PSF radius %d too large", ex->F.R);
+    // error of q against the formula's: each axis' rotated offset is off by a few
+    // roundings of its terms, at most R / sigma, and q <= trunc^2 or so there
+    ex->near = 1e-14 * (1.0 + ex->F.trunc) * (1.0 + ex->F.trunc + ex->F.R / ex->F.smin);
+    ex->coef.alloc(5 * static_cast<size_t>(N));
+    const size_t tiles = static_cast<size_t>(ex->ntile) * ex->ntile;
+    ex->reach.alloc(tiles * (2 * static_cast<size_t>(ex->F.R) + 1));
+    hipLaunchKernelGGL(wdb::k_exact_coef, wdb::pix_grid(N), dim3(256), 0, s, ex->F.dev(), ex->coef.p);
+    hipLaunchKernelGGL(wdb::k_exact_reach, dim3(static_cast<unsigned>(tiles)), dim3(wdb::kT * wdb::kT), 0, s,
+                       ex->F.dev(), ex->ntile, ex->reach.p);
     for (auto* b : {&ex->u0, &ex->y, &ex->img, &ex->r, &ex->gimg, &ex->g}) b->alloc(N);
     ex->sa.alloc(N / 4 + 1);
     ex->sb.alloc(N / 4 + 1);

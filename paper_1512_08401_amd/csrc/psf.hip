@@ -62,6 +62,7 @@ void PsfField::upload(const wdb_psf_field* f, hipStream_t s) {
   const int64_t N = static_cast<int64_t>(n) * n;
   std::vector<double> c(N), sn(N);
   double smax = 0.0;
+  smin = f->sig_minor[0];
   for (int64_t i = 0; i < N; ++i) {
     const double a = f->sig_major[i], b = f->sig_minor[i], ang = f->angle[i];
     WDB_REQUIRE(std::isfinite(a) && std::isfinite(b) && std::isfinite(ang), WDB_ERR_NONFINITE,
@@ -71,6 +72,7 @@ void PsfField::upload(const wdb_psf_field* f, hipStream_t s) {
     c[i] = std::cos(ang);
     sn[i] = std::sin(ang);
     smax = std::max(smax, std::max(a, b));
+    smin = std::min(smin, std::min(a, b));
   }
   const double Rd = std::floor(f->trunc * smax);
   WDB_REQUIRE(2.0 * Rd + 1.0 <= n, WDB_ERR_SIZE,

@@ -17,20 +17,26 @@ struct PsfDev {
   const double* Z = nullptr;   // per-source normalisation sum
 };
 
-// exp(-q/2) if q <= trunc^2 else 0, for source s and offset (dy, dx).
-__device__ __forceinline__ double psf_unnormalised(const PsfDev& P, int64_t s, int dy, int dx) {
+// q of source s at offset (dy, dx); the PSF reaches the offset if q <= trunc^2.
+__device__ __forceinline__ double psf_q(const PsfDev& P, int64_t s, int dy, int dx) {
 #pragma clang fp contract(off)
   const double c = P.c[s], sn = P.s[s], a = P.sM[s], b = P.sm[s];
   const double fx = static_cast<double>(dx), fy = static_cast<double>(dy);
   const double t1 = fx * c + fy * sn;
   const double t2 = -fx * sn + fy * c;
-  const double q = t1 * t1 / (a * a) + t2 * t2 / (b * b);
+  return t1 * t1 / (a * a) + t2 * t2 / (b * b);
+}
+
+// exp(-q/2) if q <= trunc^2 else 0, for source s and offset (dy, dx).
+__device__ __forceinline__ double psf_unnormalised(const PsfDev& P, int64_t s, int dy, int dx) {
+  const double q = psf_q(P, s, dy, dx);
   return q <= P.T2 ? exp(-0.5 * q) : 0.0;
 }
 
 // Owns the uploaded field.
 struct PsfField {
   int n = 0, R = 0;
+  double smin = 0.0;    // least sigma
   double trunc = 0.0;
   DevBuf<double> sM, sm, cs, sn_, Z;
   ~PsfField();

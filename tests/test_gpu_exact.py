@@ -85,3 +85,53 @@ def test_exact_fista_matches_oracle_on_untruncated_theta(W, name, J, ista):
     E, _, _, rel = fista.duality_gap(A, x0, lam32, host(x))
     assert abs(info["objective"] - E) <= 1e-6 * E and abs(info["rel_gap"] - rel) <= 1e-3
     assert info["iters"] == iters and info["checks"] == 5
+
+
+def direct_products(field, u, v):
+    """H u and H^* v in float64, offset by offset over the box of the field's radius."""
+    g = lambda a: torch.as_tensor(np.ascontiguousarray(a, dtype=np.float64)).cuda().reshape(field.n, field.n)
+    a, b, c, s = g(field.sig_major), g(field.sig_minor), g(np.cos(field.angle)), g(np.sin(field.angle))
+    u, v = g(u), g(v)
+    R = int(np.floor(field.trunc * max(np.max(field.sig_major), np.max(field.sig_minor))))
+
+    def offsets():
+        for dy in range(-R, R + 1):
+            for dx in range(-R, R + 1):
+                t1, t2 = dx * c + dy * s, -dx * s + dy * c
+                q = t1 * t1 / (a * a) + t2 * t2 / (b * b)
+                yield dy, dx, torch.where(q <= field.trunc ** 2, torch.exp(-0.5 * q), 0.0)
+
+    Z = sum(w for _, _, w in offsets())
+    Hu, Hv = torch.zeros_like(u), torch.zeros_like(u)
+    for dy, dx, w in offsets():
+        Hu += torch.roll(w / Z * u, (dy, dx), (0, 1))
+        Hv += w / Z * torch.roll(v, (-dy, -dx), (0, 1))
+    return host(Hu).ravel(), host(Hv).ravel()
+
+
+# Radii (floor(3 sigma)) and sides of every launch: 32 x 32, 32 x 8 and 32 x 2
+# targets per block, H staged at once, in parts and not at all, H^* staged and not,
+# a side below the tile's, a PSF of one pixel and a field whose reach varies from
+# tile to tile.
+@pytest.mark.parametrize("field", [synth.psf_rotating(8, 1.0, 0.5), synth.psf_rotating(64, 0.3, 0.3),
+                                   synth.psf_rotating(64, 10.0, 1.0), synth.psf_isotropic(128, 0.5, 5.0),
+                                   synth.psf_rotating(256, 3.0, 1.0), synth.psf_rotating(512, 4.0, 1.0),
+                                   synth.psf_rotating(512, 6.0, 0.7), synth.psf_rotating(512, 11.5, 0.7),
+                                   synth.psf_rotating(256, 22.0, 1.0)],
+                         ids=lambda f: f"n{f.n}-s{float(np.max(f.sig_major)):g}")
+def test_exact_launches_match_direct_sums(W, field):
+    n = field.n
+    print(f"exact launches n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    u, v = (rng.standard_normal(n * n).astype(np.float32) for _ in range(2))
+    Hu, Hv = direct_products(field, u, v)
+    ex = W.Exact(field, "haar", 1)
+    # float64 sums rounded once to float32 (half an ulp, 6e-8 of the value)
+    assert np.max(np.abs(host(ex.apply(dev(u))) - Hu)) <= 1e-7 * np.max(np.abs(Hu))
+    assert np.max(np.abs(host(ex.apply(dev(v), adjoint=True)) - Hv)) <= 1e-7 * np.max(np.abs(Hv))
+    # a pixel that is not finite reaches its PSF's pixels only
+    u[n + 1] = np.inf
+    one = np.zeros(n * n)
+    one[n + 1] = 1.0
+    seen = direct_products(field, one, one)[0] != 0
+    assert np.array_equal(~np.isfinite(host(ex.apply(dev(u)))), seen)
