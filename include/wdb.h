@@ -196,7 +196,7 @@ wdb_status wdb_theta_lipschitz(wdb_theta* th, const double* start, double tol,
  * the largest eigenvalue theta of the tridiagonal projection and the residual
  * bound resid = beta_m |s_m| of its Ritz pair (some eigenvalue of
  * Theta_K^T Theta_K lies within resid of theta); a cycle restarts from the
- * top Ritz vector.  Stops when resid <= tol * theta or after max_steps steps
+ * top 20 Ritz vectors and the next Lanczos vector.  Stops when resid <= tol * theta or after max_steps steps
  * in all.  Stores L = theta + resid in the handle (an upper bound of
  * lambda_max when the Ritz pair approximates the top eigenvector, which a
  * random start gives with probability one) and returns it in L_out, with the

@@ -366,8 +366,8 @@ struct LanczosResult {
   int steps;
   bool converged;
 };
-// Restarted every `cycle` steps from the top Ritz vector (the basis then
-// holds cycle + 1 vectors of N doubles).
+// Restarted from the top Ritz vectors whenever the basis holds `cycle` vectors
+// and the next one (cycle + 1 vectors of N doubles).
 LanczosResult lanczos_max(wdb_theta* th, const double* start_host, const double* dinv_sqrt, double tol, int max_steps,
                           hipStream_t s, int cycle = 48);
 // The same for any symmetric positive semidefinite M of size N given by

@@ -518,15 +518,40 @@ __global__ __launch_bounds__(kReduceParts) void k_reduce4_final(const double* __
 // ---------------------------------------------------------------------------
 // Power iteration (float64): w = A vd; u = d .* (A^T w); vd = d .* u / ||u||.
 // ---------------------------------------------------------------------------
+// Four threads share a slot row's quads: with one thread per row a 256 x 256
+// operator has one wave per SIMD, each a chain of gathers (36 -> 12 us a product).
+constexpr int kPiRows = kBlock / 4;
+
+// Dot product of slot row q in the threads q + 64 k of a block, complete in k = 0.
+__device__ __forceinline__ double quarter_dot_f64(const SellView& A, int64_t q, const double* __restrict__ x) {
+  __shared__ double sh[kBlock];
+  const int part = threadIdx.x / kPiRows;
+  double acc = 0.0;
+  if (q < slots(A)) {
+    const int64_t sl = q >> A.cshift;
+    const int64_t end = A.soff[sl + 1] >> 2;
+    for (int64_t j = (A.soff[sl] >> 2) + (q & (A.C - 1)) + part * A.C; j < end; j += 4 * A.C) {
+      const float4 v = A.val[j];
+      const int4 c = A.col[j];
+      acc = fma(static_cast<double>(v.x), x[c.x], acc);
+      acc = fma(static_cast<double>(v.y), x[c.y], acc);
+      acc = fma(static_cast<double>(v.z), x[c.z], acc);
+      acc = fma(static_cast<double>(v.w), x[c.w], acc);
+    }
+  }
+  sh[threadIdx.x] = acc;
+  __syncthreads();
+  if (part) return 0.0;
+  return (acc + sh[threadIdx.x + kPiRows]) + (sh[threadIdx.x + 2 * kPiRows] + sh[threadIdx.x + 3 * kPiRows]);
+}
+
 __global__ __launch_bounds__(kBlock) void k_pi_fwd(SellView A, const double* __restrict__ vd, double* __restrict__ w,
                                                    double* __restrict__ partial, int64_t nblocks) {
-  const int64_t q = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-  const int64_t sl = q >> A.cshift;
-  const int lane = static_cast<int>(q & (A.C - 1));
+  const int64_t q = static_cast<int64_t>(blockIdx.x) * kPiRows + threadIdx.x % kPiRows;
+  const double acc = quarter_dot_f64(A, q, vd);
   double v[1] = {0.0};
-  if (q < slots(A)) {
+  if (threadIdx.x < kPiRows && q < slots(A)) {
     const int64_t row = slot_row(A, q);
-    const double acc = row_dot_f64(A, sl, lane, vd);
     if (row >= 0) {
       w[row] = acc;
       v[0] = acc * acc;
@@ -538,13 +563,11 @@ __global__ __launch_bounds__(kBlock) void k_pi_fwd(SellView A, const double* __r
 __global__ __launch_bounds__(kBlock) void k_pi_bwd(SellView At, const double* __restrict__ w,
                                                    const double* __restrict__ d, double* __restrict__ u,
                                                    double* __restrict__ partial, int64_t nblocks) {
-  const int64_t q = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-  const int64_t sl = q >> At.cshift;
-  const int lane = static_cast<int>(q & (At.C - 1));
+  const int64_t q = static_cast<int64_t>(blockIdx.x) * kPiRows + threadIdx.x % kPiRows;
+  double acc = quarter_dot_f64(At, q, w);
   double v[1] = {0.0};
-  if (q < slots(At)) {
+  if (threadIdx.x < kPiRows && q < slots(At)) {
     const int64_t row = slot_row(At, q);
-    double acc = row_dot_f64(At, sl, lane, w);
     if (row >= 0) {
       if (d) acc *= d[row];
       u[row] = acc;
@@ -588,9 +611,9 @@ __global__ __launch_bounds__(kBlock) void k_pi_scale(const double* __restrict__ 
   vd[i] = d ? v * d[i] : v;
 }
 
-__global__ __launch_bounds__(kBlock) void k_mul(double* __restrict__ v, const double* __restrict__ d, int64_t N) {
+__global__ __launch_bounds__(kBlock) void k_mul(const double* v, const double* __restrict__ d, double* out, int64_t N) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-  if (i < N) v[i] *= d[i];
+  if (i < N) out[i] = v[i] * d[i];
 }
 
 __global__ __launch_bounds__(kBlock) void k_copy_or_zero(const float* __restrict__ src, float* __restrict__ a,
@@ -826,6 +849,36 @@ void ensure_workspace(wdb_theta* th) {
   }
 }
 
+namespace {
+
+// Blocks of the two products of a power iteration or Lanczos step.
+int64_t pi_blocks(const wdb_theta* th) {
+  const int G = check_group(th);
+  if (G > 0) return csr_check_blocks(th, G);
+  const SellView A = view(th->A), At = view(th->At);
+  partial_blocks(A, At);
+  return (slots(A) + kPiRows - 1) / kPiRows;
+}
+
+// w = A vd; u = d .* (A^T w), with the block partials of ||w||^2 and ||u||^2.
+void launch_pi(wdb_theta* th, const double* vd, double* w, const double* d, double* u, double* part, int64_t nb,
+               hipStream_t s) {
+  const int G = check_group(th);
+  const dim3 grid(static_cast<unsigned>(nb));
+  if (G > 0) {
+    with_group(G, [&](auto g) {
+      constexpr int GG = decltype(g)::value;
+      hipLaunchKernelGGL(k_pi_fwd_csr<GG>, grid, dim3(kBlock), 0, s, cview(th->cA), vd, w, part, nb);
+      hipLaunchKernelGGL(k_pi_bwd_csr<GG>, grid, dim3(kBlock), 0, s, cview(th->cAt), w, d, u, part + nb, nb);
+    });
+  } else {
+    hipLaunchKernelGGL(k_pi_fwd, grid, dim3(kBlock), 0, s, view(th->A), vd, w, part, nb);
+    hipLaunchKernelGGL(k_pi_bwd, grid, dim3(kBlock), 0, s, view(th->At), w, d, u, part + nb, nb);
+  }
+}
+
+}  // namespace
+
 double power_iteration(wdb_theta* th, const double* start_host, const double* dinv_sqrt, double tol, int max_iters,
                        int* iters_out, hipStream_t s, bool* converged_out) {
   if (converged_out) *converged_out = false;
@@ -852,10 +905,8 @@ double power_iteration(wdb_theta* th, const double* start_host, const double* di
   double* w = vd + N;
   double* u = w + N;
   WDB_HIP(hipMemcpyAsync(vd, v.data(), N * sizeof(double), hipMemcpyHostToDevice, s));
-  if (dinv_sqrt) hipLaunchKernelGGL(k_mul, vec_grid(N), dim3(kBlock), 0, s, vd, dinv_sqrt, N);
-  const SellView A = view(th->A), At = view(th->At);
-  const int G = check_group(th);
-  const int64_t nb = G > 0 ? csr_check_blocks(th, G) : partial_blocks(A, At);
+  if (dinv_sqrt) hipLaunchKernelGGL(k_mul, vec_grid(N), dim3(kBlock), 0, s, vd, dinv_sqrt, vd, N);
+  const int64_t nb = pi_blocks(th);
   double* part = th->ws_partial;
   std::vector<double> hist(kRhoChunk);
   double prev = 0.0, rho = 0.0;
@@ -863,18 +914,7 @@ double power_iteration(wdb_theta* th, const double* start_host, const double* di
   while (k < max_iters) {
     const int m = std::min(kRhoChunk, max_iters - k);
     for (int j = 0; j < m; ++j) {
-      if (G > 0) {
-        with_group(G, [&](auto g) {
-          constexpr int GG = decltype(g)::value;
-          hipLaunchKernelGGL(k_pi_fwd_csr<GG>, dim3(static_cast<unsigned>(nb)), dim3(kBlock), 0, s, cview(th->cA),
-                             vd, w, part, nb);
-          hipLaunchKernelGGL(k_pi_bwd_csr<GG>, dim3(static_cast<unsigned>(nb)), dim3(kBlock), 0, s, cview(th->cAt),
-                             w, dinv_sqrt, u, part + nb, nb);
-        });
-      } else {
-        hipLaunchKernelGGL(k_pi_fwd, slot_grid(A), dim3(kBlock), 0, s, A, vd, w, part, nb);
-        hipLaunchKernelGGL(k_pi_bwd, slot_grid(At), dim3(kBlock), 0, s, At, w, dinv_sqrt, u, part + nb, nb);
-      }
+      launch_pi(th, vd, w, dinv_sqrt, u, part, nb, s);
       hipLaunchKernelGGL(k_pi_finish, dim3(1), dim3(kBlock), 0, s, part, nb, th->ws_rho, j, th->ws_scalar);
       hipLaunchKernelGGL(k_pi_scale, vec_grid(N), dim3(kBlock), 0, s, u, dinv_sqrt, th->ws_scalar, vd, N);
     }
@@ -904,108 +944,156 @@ namespace {
 // Lanczos for lambda_max of M = D Theta_K^T Theta_K D (float64, full
 // reorthogonalisation), the largest Ritz value of the tridiagonal projection.
 // ---------------------------------------------------------------------------
-constexpr int kDotChunk = 8192;  // elements per block of the basis dot products
+// A step is bound by its passes over the basis and by launches, so it is six of
+// them: the two products, the first dots, the first update together with the second
+// dots, the second update with the norm, and the normalisation.  Each block owns a
+// chunk of the vectors and adds up the chunks' partial sums itself (in one order).
+// The host reads the coefficients two batches of steps behind the device.
+// 256 x 256, 30 nonzeros per row: 215 -> 55 us per
+// step, and 264 steps for 1711 since a restart keeps more than the top Ritz vector.
+constexpr int kLz = 512, kLzWaves = kLz / kWave;
+constexpr int kLzBatch = 4;     // steps between two reads by the host
+constexpr int kLzKeep = 20;     // Ritz vectors kept by a restart
 
-// partial[i * nchunk + c] = sum over chunk c of V_i . u, for basis vectors i < m.
-__global__ __launch_bounds__(kBlock) void k_basis_dots(const double* __restrict__ V, int64_t N,
-                                                       const double* __restrict__ u, double* __restrict__ partial,
-                                                       int64_t nchunk) {
-  const int i = blockIdx.y;
-  const double* __restrict__ v = V + static_cast<int64_t>(i) * N;
-  const int64_t beg = static_cast<int64_t>(blockIdx.x) * kDotChunk;
-  const int64_t end = min(beg + kDotChunk, N);
-  double acc = 0.0;
-  for (int64_t k = beg + threadIdx.x; k < end; k += kBlock) acc = fma(v[k], u[k], acc);
-  double vv[1] = {acc};
-  __shared__ double sh[kWaves];
-  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  for (int off = kWave / 2; off > 0; off >>= 1) vv[0] += __shfl_xor(vv[0], off);
-  if (lane == 0) sh[wid] = vv[0];
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double t = sh[0];
-    for (int w = 1; w < kWaves; ++w) t += sh[w];
-    partial[static_cast<int64_t>(i) * nchunk + blockIdx.x] = t;
+// Elements per block: at most 256 chunks.
+int64_t lz_chunk(int64_t N) { return std::max<int64_t>(kLz, ((N + 255) / 256 + kLz - 1) / kLz * kLz); }
+
+// partial[i * gridDim.x + block] = sum over the block's chunk of V_i . u, i < m: a
+// wave takes four vectors at a time.
+__device__ __forceinline__ void lz_dots(const double* __restrict__ V, int64_t N, const double* u, int m, int64_t beg,
+                                        int64_t end, double* __restrict__ partial) {
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  for (int base = 4 * wave; base < m; base += 4 * kLzWaves) {
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    const double* __restrict__ p[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) p[t] = V + static_cast<int64_t>(min(base + t, m - 1)) * N;
+#pragma unroll 8
+    for (int64_t k = beg + lane; k < end; k += kWave) {
+      const double x = u[k];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[t] = fma(p[t][k], x, acc[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      for (int off = kWave / 2; off > 0; off >>= 1) acc[t] += __shfl_xor(acc[t], off);
+      if (lane == 0 && base + t < m) partial[static_cast<int64_t>(base + t) * gridDim.x + blockIdx.x] = acc[t];
+    }
   }
 }
 
-// h[i] = sum_c partial[i * nchunk + c], one block per basis vector (fixed order).
-__global__ __launch_bounds__(kBlock) void k_basis_dots_fin(const double* __restrict__ partial, int64_t nchunk,
-                                                           double* __restrict__ h) {
-  __shared__ double sh[kBlock];
-  double acc = 0.0;
-  for (int64_t c = threadIdx.x; c < nchunk; c += kBlock) acc += partial[static_cast<int64_t>(blockIdx.x) * nchunk + c];
-  sh[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = kBlock / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) h[blockIdx.x] = sh[0];
+__global__ __launch_bounds__(kLz) void k_lz_dots(const double* __restrict__ V, int64_t N, const double* __restrict__ u,
+                                                 int m, int64_t chunk, double* __restrict__ partial) {
+  const int64_t beg = blockIdx.x * chunk;
+  lz_dots(V, N, u, m, beg, min(beg + chunk, N), partial);
 }
 
-// u -= sum_{i < m} h[i] V_i, and the block partials of ||u||^2 after the update.
-__global__ __launch_bounds__(kBlock) void k_basis_orth(const double* __restrict__ V, int64_t N, int m,
-                                                       const double* __restrict__ h, double* __restrict__ u,
-                                                       double* __restrict__ partial, int64_t nblocks) {
-  const int64_t k = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-  double v[1] = {0.0};
-  if (k < N) {
+// u -= sum_{i < m} h_i V_i with h the sums of `in`, then either the partial dots of
+// the new u (DOTS) or its partial ||u||^2; *last = h_{m - 1}.
+template <bool DOTS>
+__global__ __launch_bounds__(kLz) void k_lz_orth(const double* __restrict__ V, int64_t N, int m, int64_t chunk,
+                                                 const double* __restrict__ in, double* u, double* __restrict__ out,
+                                                 double* __restrict__ last) {
+  extern __shared__ double h[];   // m
+  __shared__ double sh[kLzWaves];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const int nchunk = static_cast<int>(gridDim.x);
+  for (int i = wave; i < m; i += kLzWaves) {
+    double t = 0.0;
+    for (int c = lane; c < nchunk; c += kWave) t += in[static_cast<int64_t>(i) * nchunk + c];
+    for (int off = kWave / 2; off > 0; off >>= 1) t += __shfl_xor(t, off);
+    if (lane == 0) h[i] = t;
+  }
+  __syncthreads();
+  if (blockIdx.x == 0 && threadIdx.x == 0) *last = h[m - 1];
+  const int64_t beg = blockIdx.x * chunk, end = min(beg + chunk, N);
+  double sq = 0.0;
+  for (int64_t k = beg + threadIdx.x; k < end; k += kLz) {
     double acc = u[k];
+#pragma unroll 16
     for (int i = 0; i < m; ++i) acc = fma(-h[i], V[static_cast<int64_t>(i) * N + k], acc);
     u[k] = acc;
-    v[0] = acc * acc;
+    sq = fma(acc, acc, sq);
   }
-  block_partials<1, 0u>(v, partial, nblocks);
+  if (DOTS) {
+    __syncthreads();
+    lz_dots(V, N, u, m, beg, end, out);
+  } else {
+    for (int off = kWave / 2; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
+    if (lane == 0) sh[wave] = sq;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double t = sh[0];
+      for (int w = 1; w < kLzWaves; ++w) t += sh[w];
+      out[blockIdx.x] = t;
+    }
+  }
 }
 
-// dst = src * scal[0]; vd = d .* dst (or dst; vd may alias src).
-__global__ __launch_bounds__(kBlock) void k_basis_next(const double* src, const double* __restrict__ scal,
-                                                       double* __restrict__ dst, const double* __restrict__ d,
-                                                       double* vd, int64_t N) {
-  const int64_t k = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-  if (k >= N) return;
-  const double v = src[k] * scal[0];
-  dst[k] = v;
-  vd[k] = d ? v * d[k] : v;
-}
-
-// out = sum_{i < m} s[i] V_i (the Ritz vector of the restart).
-__global__ __launch_bounds__(kBlock) void k_ritz_vector(const double* __restrict__ V, int64_t N, int m,
-                                                        const double* __restrict__ sv, double* __restrict__ out) {
-  const int64_t k = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-  if (k >= N) return;
-  double acc = 0.0;
-  for (int i = 0; i < m; ++i) acc = fma(sv[i], V[static_cast<int64_t>(i) * N + k], acc);
-  out[k] = acc;
-}
-
-// Block partials of ||u||^2.
-__global__ __launch_bounds__(kBlock) void k_sq_partials(const double* __restrict__ u, int64_t N,
-                                                        double* __restrict__ partial, int64_t nblocks) {
-  const int64_t k = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-  double v[1] = {k < N ? u[k] * u[k] : 0.0};
-  block_partials<1, 0u>(v, partial, nblocks);
-}
-
-// scal[0] = 1 / sqrt(sum of partials) (0 for a zero vector), scal[1] = the norm.
-__global__ __launch_bounds__(kBlock) void k_inv_norm(const double* __restrict__ partial, int64_t nblocks,
-                                                     double* __restrict__ scal) {
+// dst = u / ||u|| (0 for a zero u), ||u||^2 the sum of npart; rec = {alpha, ||u||}.
+__global__ __launch_bounds__(kBlock) void k_lz_next(const double* __restrict__ u, const double* __restrict__ npart,
+                                                    int nchunk, const double* __restrict__ hlast,
+                                                    double* __restrict__ dst, double* __restrict__ rec, int64_t N) {
   __shared__ double sh[kBlock];
-  double a = 0.0;
-  for (int64_t i = threadIdx.x; i < nblocks; i += kBlock) a += partial[i];
-  sh[threadIdx.x] = a;
+  sh[threadIdx.x] = threadIdx.x < nchunk ? npart[threadIdx.x] : 0.0;   // nchunk <= kBlock
   __syncthreads();
   for (int w = kBlock / 2; w > 0; w >>= 1) {
     if (threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    const double nrm = sqrt(sh[0]);
-    scal[0] = nrm > 0.0 ? 1.0 / nrm : 0.0;
-    scal[1] = nrm;
+  const double nrm = sqrt(sh[0]), inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
+  const int64_t k = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
+  if (k < N) dst[k] = u[k] * inv;
+  if (k == 0) {
+    rec[0] = hlast[0] + hlast[1];
+    rec[1] = nrm;
   }
 }
+
+// V_j = sum_{i < m} C[i][j] V_i for j < l, in place, and V_l = V_m.
+__global__ __launch_bounds__(kBlock) void k_lz_restart(double* __restrict__ V, int64_t N, int m, int l,
+                                                       const double* __restrict__ C) {
+  const int64_t k = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
+  if (k >= N) return;
+  double acc[kLzKeep];
+#pragma unroll
+  for (int j = 0; j < kLzKeep; ++j) acc[j] = 0.0;
+  for (int i = 0; i < m; ++i) {
+    const double v = V[static_cast<int64_t>(i) * N + k];
+#pragma unroll
+    for (int j = 0; j < kLzKeep; ++j)
+      if (j < l) acc[j] = fma(C[i * l + j], v, acc[j]);
+  }
+  const double next = V[static_cast<int64_t>(m) * N + k];
+#pragma unroll
+  for (int j = 0; j < kLzKeep; ++j)
+    if (j < l) V[static_cast<int64_t>(j) * N + k] = acc[j];
+  V[static_cast<int64_t>(l) * N + k] = next;
+}
+
+// Pinned records of a cycle's steps and the events of two batches.
+struct LzHost {
+  double* rec = nullptr;
+  hipEvent_t ev[2] = {nullptr, nullptr};
+  hipStream_t s;
+  LzHost(int k, hipStream_t stream) : s(stream) {
+    try {
+      WDB_HIP(hipHostMalloc(reinterpret_cast<void**>(&rec), 2 * static_cast<size_t>(k) * sizeof(double),
+                            hipHostMallocDefault));
+      for (auto& e : ev) WDB_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    } catch (...) {
+      release();
+      throw;
+    }
+  }
+  ~LzHost() { release(); }
+  void release() {
+    (void)hipStreamSynchronize(s);   // nothing writes to rec any more
+    for (auto& e : ev)
+      if (e) (void)hipEventDestroy(e);
+    if (rec) (void)hipHostFree(rec);
+  }
+};
 
 }  // namespace
 
@@ -1028,74 +1116,95 @@ LanczosResult lanczos_core(int64_t N, const std::function<void(const double*, do
   nrm = std::sqrt(nrm);
   WDB_REQUIRE(nrm > 0.0, WDB_ERR_ARG, "Lanczos start vector is zero");
   for (double& x : v) x /= nrm;
-  // a cycle builds at most k steps from its start vector, then restarts from
-  // the top Ritz vector: the basis holds k + 1 vectors of N doubles
+  // a cycle fills the basis to k vectors and the next one, then restarts from the
+  // top Ritz vectors
   const int k = static_cast<int>(std::min<int64_t>(std::max(cycle, 2), N));
+  const int64_t chunk = lz_chunk(N);
+  const unsigned nchunk = static_cast<unsigned>((N + chunk - 1) / chunk);
   DevBuf<double> V(static_cast<size_t>(k + 1) * N);
   DevBuf<double> ub(N);
   double* u = ub.p;
-  const int64_t nchunk = (N + kDotChunk - 1) / kDotChunk;
-  DevBuf<double> dpart(static_cast<size_t>(k + 1) * nchunk);
-  DevBuf<double> hh(2 * static_cast<size_t>(k + 1));
-  DevBuf<double> sv(static_cast<size_t>(k + 1));
-  const int64_t nbv = vec_grid(N).x;
-  DevBuf<double> npart(nbv);
-  DevBuf<double> scal(2);
+  DevBuf<double> dots(2 * static_cast<size_t>(k) * nchunk);
+  double *dots1 = dots.p, *dots2 = dots.p + static_cast<size_t>(k) * nchunk;
+  DevBuf<double> npart(nchunk);
+  DevBuf<double> hlast(2);
+  DevBuf<double> rec(2 * static_cast<size_t>(k));
+  DevBuf<double> C(static_cast<size_t>(k) * kLzKeep);
+  LzHost host(k, s);
   WDB_HIP(hipMemcpyAsync(V.p, v.data(), N * sizeof(double), hipMemcpyHostToDevice, s));
+  WDB_HIP(hipStreamSynchronize(s));
   LanczosResult res{0.0, 0.0, 0, false};
-  double hstep[2], bn[2];
-  while (res.steps < max_steps) {
-    std::vector<double> alpha, beta;
-    TopRitz tr{0.0, 1.0, {}};
-    bool done = false;
-    for (int j = 0; j < k && res.steps < max_steps; ++j) {
-      apply(V.p + static_cast<int64_t>(j) * N, u);   // u = M v_j
-      // two passes of classical Gram-Schmidt against v_0..v_j; the
-      // coefficients of v_j add up to alpha_j
-      const int m = j + 1;
-      for (int pass = 0; pass < 2; ++pass) {
-        hipLaunchKernelGGL(k_basis_dots, dim3(static_cast<unsigned>(nchunk), static_cast<unsigned>(m)), dim3(kBlock),
-                           0, s, V.p, N, u, dpart.p, nchunk);
-        hipLaunchKernelGGL(k_basis_dots_fin, dim3(static_cast<unsigned>(m)), dim3(kBlock), 0, s, dpart.p, nchunk,
-                           hh.p + pass * (k + 1));
-        hipLaunchKernelGGL(k_basis_orth, vec_grid(N), dim3(kBlock), 0, s, V.p, N, m, hh.p + pass * (k + 1), u,
-                           npart.p, nbv);
-      }
-      hipLaunchKernelGGL(k_inv_norm, dim3(1), dim3(kBlock), 0, s, npart.p, nbv, scal.p);
+  const auto step = [&](int j) {   // v_{j + 1}, alpha_j and beta_j from v_0 .. v_j
+    const int m = j + 1;
+    const size_t hb = static_cast<size_t>(m) * sizeof(double);
+    apply(V.p + static_cast<int64_t>(j) * N, u);
+    hipLaunchKernelGGL(k_lz_dots, dim3(nchunk), dim3(kLz), 0, s, V.p, N, u, m, chunk, dots1);
+    hipLaunchKernelGGL(k_lz_orth<true>, dim3(nchunk), dim3(kLz), hb, s, V.p, N, m, chunk, dots1, u, dots2, hlast.p);
+    hipLaunchKernelGGL(k_lz_orth<false>, dim3(nchunk), dim3(kLz), hb, s, V.p, N, m, chunk, dots2, u, npart.p,
+                       hlast.p + 1);
+    hipLaunchKernelGGL(k_lz_next, vec_grid(N), dim3(kBlock), 0, s, u, npart.p, static_cast<int>(nchunk), hlast.p,
+                       V.p + static_cast<int64_t>(j + 1) * N, rec.p + 2 * j, N);
+  };
+  std::vector<double> alpha, beta;
+  bool done = false;
+  while (!done && res.steps < max_steps) {
+    // steps first .. last - 1 of this cycle, kLzBatch at a time: batch b + 1 is
+    // enqueued before batch b is read
+    const int first = static_cast<int>(alpha.size());
+    const int last = std::min(k, first + (max_steps - res.steps));
+    const auto enqueue = [&](int b) {
+      const int from = first + b * kLzBatch, to = std::min(last, from + kLzBatch);
+      if (from >= last) return;
+      for (int j = from; j < to; ++j) step(j);
       WDB_HIP(hipGetLastError());
-      WDB_HIP(hipMemcpyAsync(&hstep[0], hh.p + j, sizeof(double), hipMemcpyDeviceToHost, s));
-      WDB_HIP(hipMemcpyAsync(&hstep[1], hh.p + (k + 1) + j, sizeof(double), hipMemcpyDeviceToHost, s));
-      WDB_HIP(hipMemcpyAsync(bn, scal.p, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
-      WDB_HIP(hipStreamSynchronize(s));
-      ++res.steps;
-      alpha.push_back(hstep[0] + hstep[1]);
-      WDB_REQUIRE(std::isfinite(alpha.back()) && std::isfinite(bn[1]), WDB_ERR_DIVERGED,
-                  "Lanczos produced a non-finite value");
-      const double bj = bn[1];
-      tr = top_ritz(alpha, beta);
-      res.theta = tr.theta;
-      res.resid = bj * std::fabs(tr.last);
-      if (res.resid <= tol * std::fabs(tr.theta) || bj == 0.0) {
-        res.converged = true;
-        done = true;
-        break;
+      WDB_HIP(hipMemcpyAsync(host.rec + 2 * from, rec.p + 2 * from, 2 * (to - from) * sizeof(double),
+                             hipMemcpyDeviceToHost, s));
+      WDB_HIP(hipEventRecord(host.ev[b % 2], s));
+    };
+    TopRitz tr{0.0, 1.0, {}};
+    double bj = 0.0;
+    bool broke = false;   // the basis spans an invariant space to rounding: v_{j + 1} is noise
+    enqueue(0);
+    for (int b = 0; first + b * kLzBatch < last && !done && !broke; ++b) {
+      enqueue(b + 1);
+      WDB_HIP(hipEventSynchronize(host.ev[b % 2]));
+      for (int j = first + b * kLzBatch; j < std::min(last, first + (b + 1) * kLzBatch); ++j) {
+        ++res.steps;
+        alpha.push_back(host.rec[2 * j]);
+        bj = host.rec[2 * j + 1];
+        WDB_REQUIRE(std::isfinite(alpha.back()) && std::isfinite(bj), WDB_ERR_DIVERGED,
+                    "Lanczos produced a non-finite value");
+        tr = top_ritz(alpha, beta);
+        res.theta = tr.theta;
+        res.resid = bj * std::fabs(tr.last);
+        if (res.resid <= tol * std::fabs(tr.theta) || bj == 0.0) {
+          res.converged = true;
+          done = true;
+          break;
+        }
+        if (bj <= 1e-13 * std::fabs(tr.theta)) {
+          broke = true;
+          break;
+        }
+        beta.push_back(bj);
       }
-      beta.push_back(bj);
-      if (j + 1 < k)   // v_{j+1} = u / beta_j
-        hipLaunchKernelGGL(k_basis_next, vec_grid(N), dim3(kBlock), 0, s, u, scal.p,
-                           V.p + static_cast<int64_t>(j + 1) * N, static_cast<const double*>(nullptr),
-                           V.p + static_cast<int64_t>(j + 1) * N, N);
     }
     if (done || res.steps >= max_steps) break;
-    // restart from the top Ritz vector V s (normalised)
-    const int m = static_cast<int>(tr.vec.size());
-    WDB_HIP(hipMemcpyAsync(sv.p, tr.vec.data(), m * sizeof(double), hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(k_ritz_vector, vec_grid(N), dim3(kBlock), 0, s, V.p, N, m, sv.p, u);
-    hipLaunchKernelGGL(k_sq_partials, vec_grid(N), dim3(kBlock), 0, s, u, N, npart.p, nbv);
-    hipLaunchKernelGGL(k_inv_norm, dim3(1), dim3(kBlock), 0, s, npart.p, nbv, scal.p);
-    hipLaunchKernelGGL(k_basis_next, vec_grid(N), dim3(kBlock), 0, s, u, scal.p, V.p, static_cast<const double*>(nullptr),
-                       V.p, N);
+    const int m = static_cast<int>(alpha.size());
+    Restart r;
+    if (broke) {   // from the top Ritz vector alone
+      r.C = tr.vec;
+    } else {
+      beta.pop_back();
+      r = restart_basis(alpha, beta, bj, std::max(1, std::min(kLzKeep, k / 2)));
+    }
+    const int l = broke ? 1 : static_cast<int>(r.a.size());
+    WDB_HIP(hipMemcpyAsync(C.p, r.C.data(), r.C.size() * sizeof(double), hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL(k_lz_restart, vec_grid(N), dim3(kBlock), 0, s, V.p, N, m, l, C.p);
     WDB_HIP(hipGetLastError());
+    WDB_HIP(hipStreamSynchronize(s));   // r.C is read, and no step is left of this cycle
+    alpha = r.a;
+    beta = r.b;
   }
   WDB_HIP(hipStreamSynchronize(s));
   return res;
@@ -1107,26 +1216,15 @@ LanczosResult lanczos_max(wdb_theta* th, const double* start_host, const double*
   const int64_t N = th->N;
   double* vd = th->ws_v64;
   double* w = vd + N;
-  const SellView A = view(th->A), At = view(th->At);
-  const int G = check_group(th);
-  const int64_t nb = G > 0 ? csr_check_blocks(th, G) : partial_blocks(A, At);
+  const int64_t nb = pi_blocks(th);
   double* part = th->ws_partial;
   // u = D A^T A D v
   auto apply = [&](const double* v, double* u) {
-    WDB_HIP(hipMemcpyAsync(vd, v, N * sizeof(double), hipMemcpyDeviceToDevice, s));
-    if (dinv_sqrt) hipLaunchKernelGGL(k_mul, vec_grid(N), dim3(kBlock), 0, s, vd, dinv_sqrt, N);
-    if (G > 0) {
-      with_group(G, [&](auto g) {
-        constexpr int GG = decltype(g)::value;
-        hipLaunchKernelGGL(k_pi_fwd_csr<GG>, dim3(static_cast<unsigned>(nb)), dim3(kBlock), 0, s, cview(th->cA), vd,
-                           w, part, nb);
-        hipLaunchKernelGGL(k_pi_bwd_csr<GG>, dim3(static_cast<unsigned>(nb)), dim3(kBlock), 0, s, cview(th->cAt), w,
-                           dinv_sqrt, u, part + nb, nb);
-      });
-    } else {
-      hipLaunchKernelGGL(k_pi_fwd, slot_grid(A), dim3(kBlock), 0, s, A, vd, w, part, nb);
-      hipLaunchKernelGGL(k_pi_bwd, slot_grid(At), dim3(kBlock), 0, s, At, w, dinv_sqrt, u, part + nb, nb);
+    if (dinv_sqrt) {
+      hipLaunchKernelGGL(k_mul, vec_grid(N), dim3(kBlock), 0, s, v, dinv_sqrt, vd, N);
+      v = vd;
     }
+    launch_pi(th, v, w, dinv_sqrt, u, part, nb, s);
   };
   return lanczos_core(N, apply, start_host, tol, max_steps, s, cycle);
 }

@@ -467,6 +467,26 @@ def test_clustered_top_eigenvalues_lanczos_vs_power_iteration(W):
     assert not r["converged"] and r["steps"] == 10 and r["theta"] <= top * (1 + 1e-15)
 
 
+@pytest.mark.parametrize("n,gap,tol", [(4, 1.0, 1e-12), (4, 1.0, 0.0), (8, 1e-4, 1e-12), (16, 1e-6, 1e-12),
+                                        (32, 1e-6, 0.0)])
+def test_lanczos_restarts_reach_the_top_singular_value(W, n, gap, tol):
+    """A basis as large as the space, several restarts towards clustered top
+    values, and runs on past convergence (tol = 0: the run either meets an
+    exactly invariant space or takes all its steps, in many cycles)."""
+    N = n * n
+    rng = np.random.default_rng(n)
+    U, V = (np.linalg.qr(rng.standard_normal((N, N)))[0] for _ in range(2))
+    sig = np.concatenate([1.0 - gap * np.arange(4), rng.uniform(0.0, 0.9, N - 4)]).clip(0.0)
+    A = ((U * sig) @ V.T).astype(np.float32).astype(np.float64)
+    th = W.Theta.from_csr(n, "haar", 1, np.arange(N + 1, dtype=np.int64) * N,
+                          np.tile(np.arange(N, dtype=np.int32), N), A.ravel())
+    ev = np.linalg.norm(A, 2) ** 2
+    r = th.lipschitz_lanczos(synth.power_start(N, 3), tol=tol, max_steps=400)
+    print(f"n={n} tol={tol}: {r}", flush=True)
+    assert r["converged"] or (tol == 0.0 and r["steps"] == 400)
+    assert abs(r["theta"] - ev) <= 1e-12 * ev and r["resid"] <= max(tol, 1e-12) * ev
+
+
 @pytest.mark.parametrize("layout", [None, (8, 3)])
 def test_objective_and_gap_match_oracle(W, p64, layout):
     """The float64 stopping test on the default layout and on the tiled one
