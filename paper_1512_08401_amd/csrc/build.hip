@@ -15,17 +15,26 @@
 //    periodic index arithmetic, so every non-zero <psi_a, H psi_b> of the
 //    column is produced exactly once.
 //
-// One workgroup owns one column at a time (float64 window buffers in a
-// per-workgroup slab of global memory).  The K largest magnitudes are found
-// by a radix select on the IEEE bit pattern of |theta|: each histogram pass
-// recomputes every column and counts 12-bit digits of the keys that match
-// the prefix fixed so far; once the boundary digit holds few enough entries,
-// an emit pass writes the entries above the boundary and collects the
-// boundary digit, whose ties are ordered by (|theta| descending, a*N + b
-// ascending).  The kept triples are then sorted into CSR.
+// One workgroup owns one column at a time (float64 window buffers in LDS, or in
+// a per-workgroup slab of global memory where they do not fit).  The K largest
+// magnitudes are found by a radix select on the IEEE bit pattern of |theta|: each
+// histogram pass recomputes every column and counts 12-bit digits of the keys
+// that match the prefix fixed so far; once the boundary digit holds few enough
+// entries, an emit pass writes the entries above the boundary and collects the
+// boundary digit, of which the same select on the collected list then keeps the
+// entries by (|theta| descending, a*N + b ascending).  The kept triples are
+// then sorted into CSR.
+//
+// A column is bound by its weights: every one of them is met by hundreds of
+// columns.  So they are computed once into a table (all offsets of all sources),
+// and a column reads only the offsets that lie in its atom and that any source
+// nearby reaches.  The sums keep their terms and their order.  256 x 256,
+// sigma 3 and 1, db4, 4 levels: a pass over all columns 48 -> 16 ms, the kept
+// part of the boundary (a sort on the host before) 110 -> 0.5 ms.
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <cstring>
 #include <numeric>
 
 #include "common.hpp"
@@ -123,18 +132,126 @@ __device__ inline void handle(const Select& S, double v, double sb, int a, int b
   }
 }
 
-__global__ __launch_bounds__(256) void k_theta_columns(Geom G, PsfDev P, const double* __restrict__ ftab,
-                                                       double* __restrict__ scratch, int64_t cap,
+// Normalised weights of all sources: wt[((dy + R) (2R + 1) + dx + R) N + s].
+__global__ __launch_bounds__(256) void k_weights(PsfDev P, double* __restrict__ wt) {
+  const int64_t N = static_cast<int64_t>(P.n) * P.n;
+  const int64_t s = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (s >= N) return;
+  const int dy = static_cast<int>(blockIdx.y) - P.R;
+  for (int dx = -P.R; dx <= P.R; ++dx) {
+    const double w = psf_unnormalised(P, s, dy, dx);
+    wt[(static_cast<int64_t>(blockIdx.y) * (2 * P.R + 1) + dx + P.R) * N + s] = w != 0.0 ? w / P.Z[s] : 0.0;
+  }
+}
+
+constexpr int kReach = 16;   // side of the tiles whose reach is kept
+
+// Table of the field's weights and, per row offset and kReach x kReach tile
+// (source rows, target columns), the column offsets with a weight other than 0.
+struct Weights {
+  const double* wt = nullptr;   // nullptr: weights are evaluated where they are used
+  short2* reach = nullptr;      // [dy + R][row tile][column tile]
+  int tiles = 0;
+};
+
+// Reach of the sources of rows 16 blockIdx.y .. and of all columns that a target of
+// columns 16 blockIdx.x .. meets, at dy = blockIdx.z - R.
+__global__ __launch_bounds__(256) void k_weight_reach(int n, int R, Weights T) {
+  __shared__ int lo, hi;
+  if (threadIdx.x == 0) {
+    lo = R + 1;
+    hi = -R - 1;
+  }
+  __syncthreads();
+  const int64_t N = static_cast<int64_t>(n) * n;
+  const int rows = min(kReach, n), cols = min(kReach + 2 * R, n);
+  for (int e = threadIdx.x; e < rows * cols; e += blockDim.x) {
+    const int r = static_cast<int>(blockIdx.y) * kReach + e / cols;
+    const int c = (static_cast<int>(blockIdx.x) * kReach - R + e % cols) & (n - 1);
+    const double* w = T.wt + static_cast<int64_t>(blockIdx.z) * (2 * R + 1) * N + static_cast<int64_t>(r) * n + c;
+    int first = -R, last = R;
+    while (first <= R && w[(first + R) * N] == 0.0) ++first;
+    while (last >= first && w[(last + R) * N] == 0.0) --last;
+    if (first <= last) {
+      atomicMin(&lo, first);
+      atomicMax(&hi, last);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0)
+    T.reach[(static_cast<int64_t>(blockIdx.z) * T.tiles + blockIdx.y) * T.tiles + blockIdx.x] =
+        make_short2(static_cast<short>(lo), static_cast<short>(hi));
+}
+
+// H psi_b at pixel (orow, ocol) of its window: the terms in ascending (dy, dx).
+struct Atom {
+  const double *fr, *fc;   // row and column filter of length wl
+  int wl, r0, c0, hr0, hc0;
+};
+
+// From the table, where the window does not wrap onto itself.
+__device__ __forceinline__ double blurred_atom_table(const Weights& T, int n, int R, const Atom& A, int orow, int ocol) {
+  const int64_t N = static_cast<int64_t>(n) * n;
+  const int ic = (A.hc0 + ocol) & (n - 1);
+  // atom row (column) tr = orow - R - dy, tc = ocol - R - dx
+  const int dy0 = max(-R, orow - R - A.wl + 1), dy1 = min(R, orow - R);
+  const int dx0 = max(-R, ocol - R - A.wl + 1), dx1 = min(R, ocol - R);
+  double acc = 0.0;
+  for (int dy = dy0; dy <= dy1; ++dy) {
+    const int tr = orow - R - dy, sr = (A.r0 + tr) & (n - 1);
+    const short2 d = T.reach[(static_cast<int64_t>(dy + R) * T.tiles + sr / kReach) * T.tiles + ic / kReach];
+    const int lo = max(dx0, static_cast<int>(d.x)), hi = min(dx1, static_cast<int>(d.y));
+    const double vr = A.fr[tr];
+    const double* w = T.wt + (static_cast<int64_t>(dy + R) * (2 * R + 1) + R) * N + static_cast<int64_t>(sr) * n;
+    // a weight of 0 leaves acc as it is (acc is never -0, the filters are finite)
+#pragma unroll 8
+    for (int dx = lo; dx <= hi; ++dx) acc += (vr * A.fc[ocol - R - dx]) * w[dx * N + ((ic - dx) & (n - 1))];
+  }
+  return acc;
+}
+
+__device__ double blurred_atom(const PsfDev& P, int n, int R, const Atom& A, int orow, int ocol) {
+  const int ir = (A.hr0 + orow) & (n - 1), ic = (A.hc0 + ocol) & (n - 1);
+  double acc = 0.0;
+  for (int dy = -R; dy <= R; ++dy) {
+    const int tr = (ir - dy - A.r0) & (n - 1);
+    if (tr >= A.wl) continue;
+    const double vr = A.fr[tr];
+    const int sr = (A.r0 + tr) & (n - 1);
+    for (int dx = -R; dx <= R; ++dx) {
+      const int tc = (ic - dx - A.c0) & (n - 1);
+      if (tc >= A.wl) continue;
+      const int64_t s = static_cast<int64_t>(sr) * n + ((A.c0 + tc) & (n - 1));
+      const double w = psf_unnormalised(P, s, dy, dx);
+      if (w != 0.0) acc += (vr * A.fc[tc]) * (w / P.Z[s]);
+    }
+  }
+  return acc;
+}
+
+// Doubles of a column's buffers: the window, the next level's window (which also
+// takes the third, the first the second after it), the row-transformed window.
+struct Caps {
+  int64_t in = 0, out = 0, mid = 0;
+  size_t bytes() const { return static_cast<size_t>(in + out + mid) * sizeof(double); }
+};
+
+// Columns b_begin .. b_end - 1, with their buffers in LDS or in scratch.
+template <bool LDS>
+__global__ __launch_bounds__(256) void k_theta_columns(Geom G, PsfDev P, Weights T, const double* __restrict__ ftab,
+                                                       double* __restrict__ scratch, Caps cap,
                                                        int64_t b_begin, int64_t b_end, Select S,
                                                        unsigned long long* __restrict__ ghist, Emit out,
                                                        Emit bnd, int* err) {
+  extern __shared__ double win[];
   __shared__ unsigned lhist[kDigits];
   const int tid = threadIdx.x, nt = blockDim.x;
   if (S.mode == 0)
     for (int i = tid; i < kDigits; i += nt) lhist[i] = 0u;
   __syncthreads();
-  double* bufA = scratch + static_cast<size_t>(blockIdx.x) * 2 * cap;
-  double* bufB = bufA + cap;
+  double* bufA = LDS ? win : scratch + static_cast<size_t>(blockIdx.x) * (cap.in + cap.out + cap.mid);
+  double* bufB = bufA + cap.in;
+  double* mid = bufB + cap.out;
   const int n = G.n, R = G.R, L = G.L;
   for (int64_t b = b_begin + blockIdx.x; b < b_end; b += gridDim.x) {
     int k = 0;
@@ -144,44 +261,46 @@ __global__ __launch_bounds__(256) void k_theta_columns(Geom G, PsfDev P, const d
     const int64_t pos = b - G.sub_off[k];
     const int p = static_cast<int>(pos / side), q = static_cast<int>(pos % side);
     const int wl = G.flen[lev];
-    const double* fr = ftab + G.foff[lev] + (G.sub_er[k] ? wl : 0);
-    const double* fc = ftab + G.foff[lev] + (G.sub_ec[k] ? wl : 0);
     const int r0 = (p << lev) & (n - 1), c0 = (q << lev) & (n - 1);
     // H psi_b on the atom window dilated by R (whole torus if that is wider).
     const int hl = min(wl + 2 * R, n);
     const int hr0 = (r0 - R) & (n - 1), hc0 = (c0 - R) & (n - 1);
+    const Atom A{ftab + G.foff[lev] + (G.sub_er[k] ? wl : 0), ftab + G.foff[lev] + (G.sub_ec[k] ? wl : 0),
+                 wl, r0, c0, hr0, hc0};
+    const bool table = T.wt && wl + 2 * R <= n;
     for (int o = tid; o < hl * hl; o += nt) {
       const int orow = o / hl, ocol = o - orow * hl;
-      const int ir = (hr0 + orow) & (n - 1), ic = (hc0 + ocol) & (n - 1);
-      double acc = 0.0;
-      for (int dy = -R; dy <= R; ++dy) {
-        const int tr = (ir - dy - r0) & (n - 1);
-        if (tr >= wl) continue;
-        const double vr = fr[tr];
-        const int sr = (r0 + tr) & (n - 1);
-        for (int dx = -R; dx <= R; ++dx) {
-          const int tc = (ic - dx - c0) & (n - 1);
-          if (tc >= wl) continue;
-          const int64_t s = static_cast<int64_t>(sr) * n + ((c0 + tc) & (n - 1));
-          const double w = psf_unnormalised(P, s, dy, dx);
-          if (w != 0.0) acc += (vr * fc[tc]) * (w / P.Z[s]);
-        }
-      }
-      bufA[o] = acc;
+      bufA[o] = table ? blurred_atom_table(T, n, R, A, orow, ocol) : blurred_atom(P, n, R, A, orow, ocol);
     }
     __syncthreads();
-    // Local analysis pyramid of the window.
+    // Local analysis pyramid of the window: rows, then columns.
     Win inr{hr0, hl, n}, inc{hc0, hl, n};
     double* in = bufA;
     double* ob = bufB;
     for (int lv = 1; lv <= G.J; ++lv) {
       const int M = n >> (lv - 1), Mh = M >> 1;
       const Win onr = next_win(inr, L), onc = next_win(inc, L);
-      const int cnt = onr.len * onc.len;
-      if (cnt > cap) {
+      const int cnt = onr.len * onc.len, rows = inr.len * onc.len;
+      if (cnt > (lv % 2 ? cap.out : cap.in) || 2 * rows > cap.mid) {
         if (tid == 0) atomicOr(err, 1);
         break;
       }
+      for (int o = tid; o < rows; o += nt) {
+        const int rr = o / onc.len, oj = o - rr * onc.len;
+        const int Jc = (onc.s + oj) & (Mh - 1);
+        const double* rowp = in + static_cast<size_t>(rr) * inc.len;
+        double lo = 0.0, hi = 0.0;
+        for (int m2 = 0; m2 < L; ++m2) {
+          const int cc = (2 * Jc + m2 - inc.s) & (M - 1);
+          if (cc >= inc.len) continue;
+          const double v = rowp[cc];
+          lo += G.h[m2] * v;
+          hi += G.g[m2] * v;
+        }
+        mid[2 * o] = lo;
+        mid[2 * o + 1] = hi;
+      }
+      __syncthreads();
       const int ks = 1 + (G.J - lv) * 3;
       for (int o = tid; o < cnt; o += nt) {
         const int oi = o / onc.len, oj = o - oi * onc.len;
@@ -190,15 +309,7 @@ __global__ __launch_bounds__(256) void k_theta_columns(Geom G, PsfDev P, const d
         for (int m = 0; m < L; ++m) {
           const int rr = (2 * I + m - inr.s) & (M - 1);
           if (rr >= inr.len) continue;
-          const double* rowp = in + static_cast<size_t>(rr) * inc.len;
-          double lo = 0.0, hi = 0.0;
-          for (int m2 = 0; m2 < L; ++m2) {
-            const int cc = (2 * Jc + m2 - inc.s) & (M - 1);
-            if (cc >= inc.len) continue;
-            const double v = rowp[cc];
-            lo += G.h[m2] * v;
-            hi += G.g[m2] * v;
-          }
+          const double lo = mid[2 * (rr * onc.len + oj)], hi = mid[2 * (rr * onc.len + oj) + 1];
           a00 += G.h[m] * lo;
           a01 += G.h[m] * hi;
           a10 += G.g[m] * lo;
@@ -224,6 +335,60 @@ __global__ __launch_bounds__(256) void k_theta_columns(Geom G, PsfDev P, const d
     for (int i = tid; i < kDigits; i += nt)
       if (lhist[i]) atomicAdd(&ghist[i], static_cast<unsigned long long>(lhist[i]));
   }
+}
+
+// The collected boundary entries (COO, col < N): their ranked magnitude, or with
+// `index` their linear index a * N + b.
+struct Boundary {
+  Emit e;
+  int64_t N, count;
+  const double* sigma;   // sigma_b of column b, nullptr: 1
+};
+
+__device__ __forceinline__ unsigned long long boundary_key(const Boundary& B, int64_t i) {
+  const double v = fabs(B.e.val[i]);
+  return static_cast<unsigned long long>(__double_as_longlong(B.sigma ? v * B.sigma[B.e.col[i]] : v));
+}
+
+__device__ __forceinline__ unsigned long long boundary_index(const Boundary& B, int64_t i) {
+  return static_cast<unsigned long long>(static_cast<int64_t>(B.e.row[i]) * B.N + B.e.col[i]);
+}
+
+// Counts a digit: of the magnitudes whose bits above it equal `prefix`; with INDEX
+// of the linear indices whose bits above it equal `prefix`, among the entries of
+// magnitude `key`.
+template <bool INDEX>
+__global__ __launch_bounds__(256) void k_boundary_digits(Boundary B, unsigned long long key, unsigned long long prefix,
+                                                         int shift, int width, unsigned long long* __restrict__ ghist) {
+  __shared__ unsigned lhist[kDigits];
+  for (int i = threadIdx.x; i < kDigits; i += blockDim.x) lhist[i] = 0u;
+  __syncthreads();
+  const int64_t step = static_cast<int64_t>(gridDim.x) * blockDim.x;
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < B.count; i += step) {
+    if (INDEX && boundary_key(B, i) != key) continue;
+    const unsigned long long x = (INDEX ? boundary_index(B, i) : boundary_key(B, i)) >> shift;
+    if ((x >> width) == prefix) atomicAdd(&lhist[x & ((1ull << width) - 1ull)], 1u);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < kDigits; i += blockDim.x)
+    if (lhist[i]) atomicAdd(&ghist[i], static_cast<unsigned long long>(lhist[i]));
+}
+
+// Appends the entries above `key`, and those of `key` up to the linear index `last`.
+__global__ __launch_bounds__(256) void k_boundary_keep(Boundary B, unsigned long long key, unsigned long long last,
+                                                       Emit out, int* err) {
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  bool want = false;
+  int a = 0, b = 0;
+  double v = 0.0;
+  if (i < B.count) {
+    a = B.e.row[i];
+    b = B.e.col[i];
+    v = B.e.val[i];
+    const unsigned long long k = boundary_key(B, i);
+    want = k > key || (k == key && boundary_index(B, i) <= last);
+  }
+  emit_one(want, a, b, v, out, err);
 }
 
 // Level-l equivalent filters (index l = 1..J): phi_l = cascade of h,
@@ -255,48 +420,132 @@ void level_filters(const Filter& f, int n, int J, std::vector<double>& tab, Geom
   }
 }
 
-// Largest window side reached anywhere in a column's pyramid.
-int max_window_side(const Geom& G) {
-  int best = 0;
-  for (int l = 1; l <= G.J; ++l) {
-    const int hl = std::min(G.flen[l] + 2 * G.R, G.n);
-    best = std::max(best, hl);
-    int cur_len = hl, M = G.n;
-    for (int lv = 1; lv <= G.J; ++lv) {
-      int worst = 0;
-      for (int s = 0; s < 2; ++s) worst = std::max(worst, next_win(Win{s, cur_len, M}, G.L).len);
-      cur_len = worst;
-      M >>= 1;
-      best = std::max(best, cur_len);
-    }
+// For a level-l column.
+Caps window_caps(const Geom& G, int l) {
+  int len = std::min(G.flen[l] + 2 * G.R, G.n), M = G.n;
+  Caps c;
+  c.in = static_cast<int64_t>(len) * len;
+  for (int lv = 1; lv <= G.J; ++lv) {
+    int next = 0;
+    for (int s = 0; s < 2; ++s) next = std::max(next, next_win(Win{s, len, M}, G.L).len);
+    c.mid = std::max(c.mid, 2 * static_cast<int64_t>(len) * next);
+    int64_t& to = lv % 2 ? c.out : c.in;
+    to = std::max(to, static_cast<int64_t>(next) * next);
+    len = next;
+    M >>= 1;
   }
-  return best;
+  return c;
 }
+
+Caps larger(const Caps& a, const Caps& b) {
+  return Caps{std::max(a.in, b.in), std::max(a.out, b.out), std::max(a.mid, b.mid)};
+}
+
+// LDS for the window buffers of a block: three blocks per CU beside their digit counts.
+constexpr size_t kWindowLds = 36 * 1024;
 
 struct Builder {
   Geom G{};
   PsfField psf;
-  DevBuf<double> ftab, scratch;
+  DevBuf<double> ftab, scratch, wt;
+  DevBuf<short2> reach;
   DevBuf<unsigned long long> hist, counters;
   DevBuf<int> err;
-  int64_t cap = 0;
+  Weights T;
+  Caps cap;               // of the columns in scratch
+  int64_t lds_begin = 0;  // first of the columns in LDS (the finer levels)
   int nwg = 0;
   hipStream_t s = nullptr;
   bool log = false;
 
+  // The weights' table, where it takes no more than a quarter of the memory that
+  // is free beside the kept entries.
+  void tabulate(int64_t nnz_budget) {
+    const int64_t N = static_cast<int64_t>(G.n) * G.n, span = 2 * G.R + 1;
+    size_t free = 0, all = 0;
+    WDB_HIP(hipMemGetInfo(&free, &all));
+    const size_t entry = 2 * sizeof(int32_t) + sizeof(double);
+    const size_t kept = (static_cast<size_t>(nnz_budget) + kBoundaryCap) * entry;
+    if (free < kept || static_cast<size_t>(span * span * N) > (free - kept) / 4 / sizeof(double)) return;
+    wt.alloc(span * span * N);
+    T.tiles = (G.n + kReach - 1) / kReach;
+    reach.alloc(static_cast<size_t>(span) * T.tiles * T.tiles);
+    T.wt = wt.p;
+    T.reach = reach.p;
+    hipLaunchKernelGGL(k_weights, dim3(static_cast<unsigned>((N + 255) / 256), static_cast<unsigned>(span)), dim3(256),
+                       0, s, psf.dev(), wt.p);
+    hipLaunchKernelGGL(k_weight_reach, dim3(T.tiles, T.tiles, static_cast<unsigned>(span)), dim3(256), 0, s, G.n, G.R,
+                       T);
+    WDB_HIP(hipGetLastError());
+  }
+
+  void columns(int64_t b0, int64_t b1, int blocks, const Select& S, Emit out, Emit bnd) {
+    if (b0 < std::min(b1, lds_begin))
+      hipLaunchKernelGGL(k_theta_columns<false>, dim3(blocks), dim3(256), 0, s, G, psf.dev(), T, ftab.p, scratch.p,
+                         cap, b0, std::min(b1, lds_begin), S, hist.p, out, bnd, err.p);
+    for (int l = G.J; l >= 1; --l) {   // a level's own buffers: the finer, the more blocks per CU
+      const int k = 1 + (G.J - l) * 3;
+      const int64_t from = std::max({b0, lds_begin, G.sub_off[l == G.J ? 0 : k]}), to = std::min(b1, G.sub_off[k + 3]);
+      const Caps c = window_caps(G, l);
+      if (from < to)
+        hipLaunchKernelGGL(k_theta_columns<true>, dim3(blocks), dim3(256), c.bytes(), s, G, psf.dev(), T, ftab.p,
+                           scratch.p, c, from, to, S, hist.p, out, bnd, err.p);
+    }
+    WDB_HIP(hipGetLastError());
+  }
+
   void run(const Select& S, Emit out, Emit bnd) {
     const int64_t N = static_cast<int64_t>(G.n) * G.n;
     const int64_t chunk = 32768;
-    for (int64_t b0 = 0; b0 < N; b0 += chunk) {
-      const int64_t b1 = std::min(N, b0 + chunk);
-      hipLaunchKernelGGL(k_theta_columns, dim3(nwg), dim3(256), 0, s, G, psf.dev(), ftab.p, scratch.p, cap, b0,
-                         b1, S, hist.p, out, bnd, err.p);
-      WDB_HIP(hipGetLastError());
-    }
+    for (int64_t b0 = 0; b0 < N; b0 += chunk) columns(b0, std::min(N, b0 + chunk), nwg, S, out, bnd);
     WDB_HIP(hipStreamSynchronize(s));
     int e = 0;
     WDB_HIP(hipMemcpy(&e, err.p, sizeof(int), hipMemcpyDeviceToHost));
     WDB_REQUIRE(e == 0, WDB_ERR_HIP, "theta build consistency check failed (code %d)", e);
+  }
+
+  // Counts of one digit, as `launch` adds them to the cleared hist.
+  template <typename F>
+  void digits(std::vector<unsigned long long>& h, F&& launch) {
+    WDB_HIP(hipMemsetAsync(hist.p, 0, kDigits * sizeof(unsigned long long), s));
+    launch();
+    WDB_HIP(hipGetLastError());
+    WDB_HIP(hipMemcpyAsync(h.data(), hist.p, kDigits * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
+    WDB_HIP(hipStreamSynchronize(s));
+  }
+
+  // Appends the `need` first entries of `B`, by magnitude descending, then linear
+  // index ascending, to out; all agree with `prefix` in the upper pbits of the
+  // magnitude.  Returns the last one's magnitude.
+  double keep_boundary(const Boundary& B, unsigned long long prefix, int pbits, unsigned long long need, Emit out) {
+    std::vector<unsigned long long> h(kDigits);
+    const dim3 grid(static_cast<unsigned>(std::min<int64_t>((B.count + 255) / 256, 1024)));
+    unsigned long long same = static_cast<unsigned long long>(B.count);   // entries with the prefix
+    while (pbits < 64) {
+      const int w = std::min(12, 64 - pbits), shift = 64 - pbits - w;
+      digits(h, [&] { hipLaunchKernelGGL(k_boundary_digits<false>, grid, dim3(256), 0, s, B, 0ull, prefix, shift, w, hist.p); });
+      int d = (1 << w) - 1;
+      while (d > 0 && h[d] < need) need -= h[d--];
+      same = h[d];
+      prefix = (prefix << w) | static_cast<unsigned long long>(d);
+      pbits += w;
+    }
+    unsigned long long last = ~0ull;
+    if (need < same) {   // equal magnitudes straddle the cut
+      last = 0;
+      for (int shift = 60; shift >= 0; shift -= 12) {
+        digits(h, [&] { hipLaunchKernelGGL(k_boundary_digits<true>, grid, dim3(256), 0, s, B, prefix, last, shift, 12, hist.p); });
+        int d = 0;
+        while (d < kDigits - 1 && h[d] < need) need -= h[d++];
+        last = (last << 12) | static_cast<unsigned long long>(d);
+      }
+    }
+    hipLaunchKernelGGL(k_boundary_keep, dim3(static_cast<unsigned>((B.count + 255) / 256)), dim3(256), 0, s, B, prefix,
+                       last, out, err.p);
+    WDB_HIP(hipGetLastError());
+    double threshold;
+    std::memcpy(&threshold, &prefix, sizeof(threshold));
+    return threshold;
   }
 };
 
@@ -380,9 +629,7 @@ void build_stationary(Builder& B, int64_t nnz_budget, int scaled, unsigned long 
     Emit out{er.p, ec.p, ev.p, B.counters.p, static_cast<unsigned long long>(N)};
     Emit none{nullptr, nullptr, nullptr, B.counters.p + 1, 0};
     Select S{2, 0, 0, 0, 0, 0};
-    hipLaunchKernelGGL(k_theta_columns, dim3(1), dim3(256), 0, s, G, B.psf.dev(), B.ftab.p, B.scratch.p, B.cap,
-                       G.sub_off[k], G.sub_off[k] + 1, S, B.hist.p, out, none, B.err.p);
-    WDB_HIP(hipGetLastError());
+    B.columns(G.sub_off[k], G.sub_off[k] + 1, 1, S, out, none);
     unsigned long long cnt = 0;
     WDB_HIP(hipMemcpyAsync(&cnt, B.counters.p, sizeof(cnt), hipMemcpyDeviceToHost, s));
     WDB_HIP(hipStreamSynchronize(s));
@@ -559,10 +806,21 @@ extern "C" wdb_status wdb_build_theta_rule(const wdb_psf_field* field, int32_t w
   level_filters(f, n, levels, tab, G);
   B.ftab.alloc(tab.size());
   WDB_HIP(hipMemcpy(B.ftab.p, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice));
-  const int side = max_window_side(G);
-  B.cap = static_cast<int64_t>(side) * side;
   B.nwg = static_cast<int>(std::min<int64_t>(1024, N));
-  B.scratch.alloc(static_cast<size_t>(B.nwg) * 2 * B.cap);
+  // columns of the levels whose windows fit go through LDS (the finer levels come last)
+  B.lds_begin = N;
+  for (int k = G.nsub - 1; k >= 0; --k) {
+    if (window_caps(G, G.sub_level[k]).bytes() > kWindowLds) break;
+    B.lds_begin = G.sub_off[k];
+  }
+  if (B.lds_begin > 0) {
+    for (int l = 1; l <= G.J; ++l) B.cap = larger(B.cap, window_caps(G, l));
+    // as many workgroups as two windows each would leave room for
+    const size_t windows = 2 * static_cast<size_t>(B.cap.in) * sizeof(double);
+    if (B.nwg * windows > (size_t{1} << 30))
+      B.nwg = std::max(1, static_cast<int>(B.nwg * windows / std::max(windows, B.cap.bytes())));
+    B.scratch.alloc(B.nwg * B.cap.bytes() / sizeof(double));
+  }
   B.hist.alloc(kDigits);
   B.counters.alloc(2);
   B.err.alloc(1);
@@ -601,6 +859,7 @@ extern "C" wdb_status wdb_build_theta_rule(const wdb_psf_field* field, int32_t w
     return WDB_OK;
   }
 
+  B.tabulate(nnz_budget);
   Emit none{nullptr, nullptr, nullptr, B.counters.p, 0};
   // Radix select of the nnz_budget-th largest |theta|.
   unsigned long long need = static_cast<unsigned long long>(nnz_budget);
@@ -656,39 +915,27 @@ extern "C" wdb_status wdb_build_theta_rule(const wdb_psf_field* field, int32_t w
               "theta emit pass produced %llu/%llu entries, expected %llu/%llu", cnt[0], cnt[1], above, bcount);
   double threshold = 0.0;
   if (!keep_all) {
-    // Order the boundary digit: |theta| descending, then linear index ascending.
-    std::vector<int32_t> hr(bcount), hc(bcount);
-    std::vector<double> hv(bcount);
-    WDB_HIP(hipMemcpy(hr.data(), brow.p, bcount * sizeof(int32_t), hipMemcpyDeviceToHost));
-    WDB_HIP(hipMemcpy(hc.data(), bcol.p, bcount * sizeof(int32_t), hipMemcpyDeviceToHost));
-    WDB_HIP(hipMemcpy(hv.data(), bval.p, bcount * sizeof(double), hipMemcpyDeviceToHost));
-    std::vector<size_t> idx(bcount);
-    std::iota(idx.begin(), idx.end(), size_t(0));
-    const std::vector<Subband> lay = layout(n, levels);
-    auto rank = [&](size_t x) {  // the ranked magnitude (times sigma_b of the column when scaled)
-      if (!scaled) return std::fabs(hv[x]);
-      int k = 0;
-      while (k + 1 < static_cast<int>(lay.size()) && hc[x] >= lay[k + 1].offset) ++k;
-      return std::fabs(hv[x]) / lay[k].side;
-    };
-    std::sort(idx.begin(), idx.end(), [&](size_t x, size_t y) {
-      const double ax = rank(x), ay = rank(y);
-      if (ax != ay) return ax > ay;
-      return static_cast<int64_t>(hr[x]) * N + hc[x] < static_cast<int64_t>(hr[y]) * N + hc[y];
-    });
-    std::vector<int32_t> sr(need), sc(need);
-    std::vector<double> sv(need);
-    for (unsigned long long i = 0; i < need; ++i) {
-      sr[i] = hr[idx[i]];
-      sc[i] = hc[idx[i]];
-      sv[i] = hv[idx[i]];
+    DevBuf<double> sigma;
+    if (scaled) {   // the ranked magnitude is times sigma_b of the column
+      std::vector<double> sg(N);
+      for (int k = 0; k < G.nsub; ++k)
+        for (int64_t b = G.sub_off[k]; b < G.sub_off[k + 1]; ++b) sg[b] = 1.0 / static_cast<double>(G.sub_side[k]);
+      sigma.alloc(N);
+      WDB_HIP(hipMemcpy(sigma.p, sg.data(), N * sizeof(double), hipMemcpyHostToDevice));
     }
-    threshold = rank(idx[need - 1]);
-    WDB_HIP(hipMemcpy(orow.p + above, sr.data(), need * sizeof(int32_t), hipMemcpyHostToDevice));
-    WDB_HIP(hipMemcpy(ocol.p + above, sc.data(), need * sizeof(int32_t), hipMemcpyHostToDevice));
-    WDB_HIP(hipMemcpy(oval.p + above, sv.data(), need * sizeof(double), hipMemcpyHostToDevice));
+    Emit rest{orow.p + above, ocol.p + above, oval.p + above, B.counters.p, need};
+    WDB_HIP(hipMemsetAsync(B.counters.p, 0, sizeof(unsigned long long), s));
+    threshold = B.keep_boundary(Boundary{eb, N, static_cast<int64_t>(bcount), sigma.p}, prefix, pbits, need, rest);
+    unsigned long long kept = 0;
+    int e = 0;
+    WDB_HIP(hipMemcpyAsync(&kept, B.counters.p, sizeof(kept), hipMemcpyDeviceToHost, s));
+    WDB_HIP(hipMemcpyAsync(&e, B.err.p, sizeof(e), hipMemcpyDeviceToHost, s));
+    WDB_HIP(hipStreamSynchronize(s));
+    WDB_REQUIRE(e == 0 && kept == need, WDB_ERR_HIP, "boundary select kept %llu entries, expected %llu (code %d)", kept,
+                need, e);
   }
   B.scratch.reset();
+  B.wt.reset();
 
   wdb_theta* th = new wdb_theta();
   try {

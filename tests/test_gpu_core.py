@@ -172,6 +172,36 @@ def test_build_theta_matches_dense_oracle(W, p64, case):
     assert abs(info["threshold"] - theta.threshold_value(T, K)) <= 1e-12 * np.max(np.abs(T))
 
 
+@pytest.mark.parametrize("rule", ["naive", "scale"])
+@pytest.mark.parametrize("field,name,J", [(synth.psf_stationary(16, 1.2, 1.2), "haar", 2),
+                                          (synth.psf_rotating(32, 2.0, 1.0), "haar", 3),
+                                          (synth.psf_rotating(32, 2.5, 0.7), "db4", 1)])
+def test_build_keeps_the_largest_entries_exactly(W, monkeypatch, field, name, J, rule):
+    """The column-by-column build of a few budgets against its own full set of
+    entries: the largest ranked magnitudes, equal ones by ascending linear index
+    (the symmetric field has many), down to the last bit."""
+    monkeypatch.setenv("WDB_BUILD_GENERAL", "1")
+    n = field.n
+    N = n * n
+    rp, cc, vv = W.build_theta(field, name, J, N * N, rule=rule).export()
+    idx = np.repeat(np.arange(N, dtype=np.int64), np.diff(rp)) * N + cc
+    mag = np.abs(vv)
+    if rule == "scale":
+        sides = [n >> J] + [n >> lev for lev in range(J, 0, -1) for _ in range(3)]
+        side = np.concatenate([np.full(t * t, t) for t in sides])
+        mag = mag / side[cc]
+    order = np.lexsort((idx, -mag))
+    first = np.flatnonzero(np.diff(mag[order]) == 0.0)   # an entry equal to the next: a cut inside equal ones
+    cuts = {1, len(vv) // 7, len(vv) - 1} | {int(first[t]) + 1 for t in (0, len(first) // 2, -1) if len(first)}
+    for K in sorted(cuts):
+        th = W.build_theta(field, name, J, K, rule=rule)
+        r, c, v = th.export()
+        keep = np.sort(order[:K])
+        assert np.array_equal(np.repeat(np.arange(N, dtype=np.int64), np.diff(r)) * N + c, idx[keep]), K
+        assert np.array_equal(v, vv[keep]), K
+        assert th.info()["threshold"] == mag[order[K - 1]], K
+
+
 @pytest.mark.parametrize("case", ["haar64_iso", "db4_32_aniso", "haar16_cut"])
 def test_convolution_build_matches_alg3_oracle(W, case):
     """A stationary field takes the fast path (one column per subband, circulant
