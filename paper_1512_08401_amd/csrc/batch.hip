@@ -20,7 +20,12 @@
 // lane = row, and for every shared column code each lane loads its column's
 // W right-hand-side values (neighbouring lanes of a tile row read neighbouring
 // columns) and the tile value once for all of them.  Their float64 checks run
-// on the tiles too.
+// on the tiles too.  The gathers are bound by the L1's lines: their eight slots
+// lie in two planes [N][4], so that each 16-byte load of a tile row is whole
+// lines, where [N][8] gives every load half of twice as many (24 problems of 256 x
+// 256, per iteration: 150 -> 129 us; with a group's operands under way while the one
+// before it is summed 129 -> 89 us, with the packs' order 89 -> 72 us).  What is
+// left is near the L1's 64 bytes a cycle and CU.
 //
 // Each problem's iterate is anchored as in the single solve: a float64 anchor
 // [N][W] plus the float32 displacement X; the residual subtracts
@@ -61,7 +66,10 @@ struct ChunkDev {
   float* Cr;         // [N][8] right-hand side of the displacement iteration, x0 - Theta_K anchor
   double* Anc;       // [N][8] float64 anchor
   float* Rr;         // [N][8] residual
+  int g0, gn;        // first chunk of the operator, and their number
   int W;             // slots in use (8, 4, 2 or 1): the vectors are [N][W], problem slots [0, W)
+  int shift;         // of W = 8: row r's slots 0 .. 3 begin at r << shift and 4 .. 7 half behind
+  int64_t half;      // ([N][8]: 3 and 4; two planes [N][4], on the tiles: 2 and 4 N)
   const float* pinv; // N or null
   float tau;
   float thr[kR];     // tau * lambda_j
@@ -82,10 +90,30 @@ struct ChunkDev {
   const float* tev[2];
 };
 
-__device__ __forceinline__ int chunk_of(const int* __restrict__ first, int nchunks, int blk) {
+// Slot j of row `row` of a chunk's block.
+template <int W>
+__device__ __forceinline__ int64_t slot_of(const ChunkDev& C, int64_t row, int j) {
+  return W == 8 ? (row << C.shift) + (j >= 4 ? C.half : 0) + (j & 3) : row * W + j;
+}
+__host__ __device__ inline int64_t slot_of(int W, bool planes, int64_t N, int64_t row, int j) {
+  return W == 8 && planes ? (j >= 4 ? 4 * N : 0) + 4 * row + (j & 3) : row * W + j;
+}
+
+// Chunk and block of the chunk of this workgroup.  An operator's chunks take turns
+// every 8 blocks (one per XCD, each with its own L2), so that they read its
+// entries together: from the memory once, then from the L2 (24 problems of 256 x 256
+// on sliced ELL, per iteration: 190 -> 98 us).  Every chunk has a multiple of 8
+// blocks.
+struct Place {
+  int c, blk;
+};
+__device__ __forceinline__ Place place_of(const ChunkDev* __restrict__ ch, const int* __restrict__ first, int nchunks) {
+  const int b = blockIdx.x;
   int c = 0;
-  while (c + 1 < nchunks && blk >= first[c + 1]) ++c;
-  return c;
+  while (c + 1 < nchunks && b >= first[c + 1]) ++c;
+  const int g0 = ch[c].g0, gn = ch[c].gn, l = b - first[g0];
+  const int turn = l >> 3;
+  return Place{g0 + turn % gn, turn / gn * 8 + (l & 7)};
 }
 
 __device__ __forceinline__ int64_t slot_row_c(const int32_t* perm, int64_t nrows, int64_t q) {
@@ -93,61 +121,133 @@ __device__ __forceinline__ int64_t slot_row_c(const int32_t* perm, int64_t nrows
   return q < nrows ? q : -1;
 }
 
-// acc[j] += w V[c][j] for the W slots of an [N][W] block (one 4-, 8-, 16- or
-// two 16-byte loads).
-template <int W>
-__device__ __forceinline__ void gatherW(const float* __restrict__ V, int c, float w, float (&acc)[kR]) {
-  const float* p = V + static_cast<int64_t>(c) * W;
-  if constexpr (W == 8) {
-    const float4 a = reinterpret_cast<const float4*>(p)[0], b = reinterpret_cast<const float4*>(p)[1];
-    acc[0] = fmaf(w, a.x, acc[0]);
-    acc[1] = fmaf(w, a.y, acc[1]);
-    acc[2] = fmaf(w, a.z, acc[2]);
-    acc[3] = fmaf(w, a.w, acc[3]);
-    acc[4] = fmaf(w, b.x, acc[4]);
-    acc[5] = fmaf(w, b.y, acc[5]);
-    acc[6] = fmaf(w, b.z, acc[6]);
-    acc[7] = fmaf(w, b.w, acc[7]);
-  } else if constexpr (W == 4) {
-    const float4 a = *reinterpret_cast<const float4*>(p);
-    acc[0] = fmaf(w, a.x, acc[0]);
-    acc[1] = fmaf(w, a.y, acc[1]);
-    acc[2] = fmaf(w, a.z, acc[2]);
-    acc[3] = fmaf(w, a.w, acc[3]);
+// The W slots of row c of a block (one 4-, 8-, 16- or two 16-byte loads), in two
+// planes (PLANES, W = 8) or side by side.
+template <int W, bool PLANES>
+__device__ __forceinline__ void loadW(const ChunkDev& C, const float* __restrict__ V, int c, float (&x)[W]) {
+  const float* p = V + static_cast<int64_t>(c) * (PLANES && W == 8 ? 4 : W);
+  if constexpr (W >= 4) {
+#pragma unroll
+    for (int h = 0; h < W / 4; ++h) {
+      const float4 a = *reinterpret_cast<const float4*>(p + h * (PLANES ? C.half : 4));
+      x[4 * h] = a.x;
+      x[4 * h + 1] = a.y;
+      x[4 * h + 2] = a.z;
+      x[4 * h + 3] = a.w;
+    }
   } else if constexpr (W == 2) {
     const float2 a = *reinterpret_cast<const float2*>(p);
-    acc[0] = fmaf(w, a.x, acc[0]);
-    acc[1] = fmaf(w, a.y, acc[1]);
+    x[0] = a.x;
+    x[1] = a.y;
   } else {
-    acc[0] = fmaf(w, p[0], acc[0]);
+    x[0] = p[0];
   }
 }
+
+// The slots of four columns, and acc += v[0] x[0] + .. + v[3] x[3].
+template <int W>
+struct Quad {
+  float x[4][W];
+  template <bool PLANES>
+  __device__ __forceinline__ void load(const ChunkDev& C, const float* __restrict__ V, const int4& col) {
+    loadW<W, PLANES>(C, V, col.x, x[0]);
+    loadW<W, PLANES>(C, V, col.y, x[1]);
+    loadW<W, PLANES>(C, V, col.z, x[2]);
+    loadW<W, PLANES>(C, V, col.w, x[3]);
+  }
+  __device__ __forceinline__ void add(const float4& v, float (&acc)[kR]) const {
+    const float w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int j = 0; j < W; ++j) acc[j] = fmaf(w[t], x[t][j], acc[j]);
+  }
+};
 
 template <int W>
-__device__ __forceinline__ void slice_mm(const int64_t* __restrict__ soff, const float4* __restrict__ val,
-                                         const int4* __restrict__ col, int64_t sl, int lane, int C,
-                                         const float* __restrict__ V, float (&acc)[kR]) {
-  const int64_t beg = soff[sl] >> 2, end = soff[sl + 1] >> 2;
-  for (int64_t j = beg + lane; j < end; j += C) {
-    const float4 v = val[j];
-    const int4 c = col[j];
-    gatherW<W>(V, c.x, v.x, acc);
-    gatherW<W>(V, c.y, v.y, acc);
-    gatherW<W>(V, c.z, v.z, acc);
-    gatherW<W>(V, c.w, v.w, acc);
+__device__ __forceinline__ void slice_mm(const ChunkDev& K, const int64_t* __restrict__ soff,
+                                         const float4* __restrict__ val, const int4* __restrict__ col, int64_t sl,
+                                         int lane, int C, const float* __restrict__ V, float (&acc)[kR]) {
+  const int64_t end = soff[sl + 1] >> 2;
+  int64_t j = (soff[sl] >> 2) + lane;
+  if (j >= end) return;
+  // one quad's columns and the indices of the one after it are on their way while
+  // a quad is summed
+  float4 v = val[j], vn;
+  int4 c = col[j];
+  Quad<W> qa, qb;
+  qa.template load<false>(K, V, c);
+  int64_t next = min(j + C, end - 1);
+  vn = val[next];
+  c = col[next];
+  const auto step = [&](Quad<W>& q, Quad<W>& qn) {   // false at the last quad
+    const bool more = j + C < end;
+    const float4 w = v;
+    v = vn;
+    if (more) {
+      qn.template load<false>(K, V, c);
+      next = min(j + 2 * C, end - 1);
+      vn = val[next];
+      c = col[next];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    q.add(w, acc);
+    j += C;
+    return more;
+  };
+  while (step(qa, qb) && step(qb, qa)) {
   }
 }
 
-// Codes and the lane's 4 values of group k of copy m: from the dense values
-// or from the kept-value layout.
-__device__ __forceinline__ void group_at(const ChunkDev& C, int m, int k, int lane, uint4& c, float4& v) {
-  if (C.tkept) {
-    const GroupRec r = C.tgrec[m][k];
-    c = r.code;
-    v = kept_values(r, C.tkval[m], C.tkbytes[m]);
-  } else {
-    c = C.tcode[m][k];
-    v = C.tval[m][static_cast<int64_t>(k) * kWave + lane];
+// Codes and the lane's 4 values of group k of copy m: from the dense values or from
+// the kept-value layout (KEPT).
+template <bool KEPT>
+struct Group {
+  GroupRec r;
+  float4 v;
+  __device__ __forceinline__ void codes(const ChunkDev& C, int m, int k, int lane) {
+    if (KEPT) {
+      r = C.tgrec[m][k];
+    } else {
+      r.code = C.tcode[m][k];
+      v = C.tval[m][static_cast<int64_t>(k) * kWave + lane];
+    }
+  }
+  __device__ __forceinline__ void values(const ChunkDev& C, int m) {
+    if (KEPT) v = ld_kept(C.tkval[m], C.tkbytes[m], kept_offset(r));
+  }
+  __device__ __forceinline__ float4 dense() const { return KEPT ? expand_kept(r.m, v) : v; }
+};
+
+// A wavefront's groups k, k + kWaves, .. of [k, end): load(x, codes) fetches a group's
+// operands into an X, add(x, values) sums them.  The next group's operands and values
+// and the codes of the one after it are under way while a group is summed (a chain
+// of three loads a group otherwise: a tile's longest lists were most of an iteration).
+template <bool KEPT, typename X, typename LOAD, typename ADD>
+__device__ __forceinline__ void for_groups(const ChunkDev& C, int m, int k, int end, int lane, LOAD&& load, ADD&& add) {
+  if (k >= end) return;
+  const int last = k + (end - 1 - k) / kWaves * kWaves;
+  Group<KEPT> a, b;
+  X xa, xb;
+  a.codes(C, m, k, lane);
+  b.codes(C, m, min(k + kWaves, last), lane);
+  a.values(C, m);
+  load(xa, a.r.code);
+  const auto step = [&](X& x, X& next) {   // false at the last group
+    Group<KEPT> c;
+    c.codes(C, m, min(k + 2 * kWaves, last), lane);
+    if (k != last) {
+      b.values(C, m);
+      load(next, b.r.code);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    add(x, a.dense());
+    a = b;
+    b = c;
+    k += kWaves;
+    return k <= last;
+  };
+  while (step(xa, xb) && step(xb, xa)) {
   }
 }
 
@@ -162,18 +262,31 @@ __device__ __forceinline__ int tile_mm(const ChunkDev& C, int m, int tile, const
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int row = tile_row(d, lane);
   const RowCode rc = tile_row_code(C.geo, d, row);
-  for (int k = (d.x >> 2) + wv; k < (d.y >> 2); k += kWaves) {
-    uint4 c;
-    float4 v;
-    group_at(C, m, k, lane, c, v);
-    const int4 col = group_cols(C.geo, rc, c);
-    gatherW<W>(V, col.x, v.x, acc);
-    gatherW<W>(V, col.y, v.y, acc);
-    gatherW<W>(V, col.z, v.z, acc);
-    gatherW<W>(V, col.w, v.w, acc);
+  const auto load = [&](Quad<W>& x, const uint4& c) { x.template load<true>(C, V, group_cols(C.geo, rc, c)); };
+  const auto add = [&](const Quad<W>& x, const float4& v) { x.add(v, acc); };
+  if (C.tkept)
+    for_groups<true, Quad<W>>(C, m, (d.x >> 2) + wv, d.y >> 2, lane, load, add);
+  else
+    for_groups<false, Quad<W>>(C, m, (d.x >> 2) + wv, d.y >> 2, lane, load, add);
+  if (row >= 0 && (d.w & kHasEsc)) {  // escapes dealt round-robin to the wavefronts, four in flight
+    const int end = C.terp[m][row + 1];
+    for (int k = C.terp[m][row] + wv; k < end; k += 4 * kWaves) {
+      int c[4];
+      float w[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        c[t] = C.tec[m][min(k + t * kWaves, end - 1)];
+        w[t] = C.tev[m][min(k + t * kWaves, end - 1)];
+      }
+      Quad<W> x;
+      x.template load<true>(C, V, make_int4(c[0], c[1], c[2], c[3]));
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (k + t * kWaves < end)
+#pragma unroll
+          for (int j = 0; j < W; ++j) acc[j] = fmaf(w[t], x.x[t][j], acc[j]);
+    }
   }
-  if (row >= 0 && (d.w & kHasEsc))  // escapes dealt round-robin to the wavefronts
-    for (int k = C.terp[m][row] + wv; k < C.terp[m][row + 1]; k += kWaves) gatherW<W>(V, C.tec[m][k], C.tev[m][k], acc);
   if constexpr (kWaves > 1) {
 #pragma unroll
     for (int j = 0; j < W; ++j) part[wv][j][lane] = acc[j];
@@ -193,13 +306,14 @@ __device__ __forceinline__ int tile_mm(const ChunkDev& C, int m, int tile, const
 // Row `row` of r = acc - c over the W slots.
 template <int W>
 __device__ __forceinline__ void store_residual(const ChunkDev& C, int64_t row, const float (&acc)[kR]) {
-  const float* b = C.Cr + row * W;
-  float* r = C.Rr + row * W;
+  const int64_t at = slot_of<W>(C, row, 0);
+  const float* b = C.Cr + at;
+  float* r = C.Rr + at;
   if constexpr (W >= 4) {
 #pragma unroll
     for (int h = 0; h < W / 4; ++h) {
-      const float4 bb = reinterpret_cast<const float4*>(b)[h];
-      reinterpret_cast<float4*>(r)[h] =
+      const float4 bb = *reinterpret_cast<const float4*>(b + h * C.half);
+      *reinterpret_cast<float4*>(r + h * C.half) =
           make_float4(acc[4 * h] - bb.x, acc[4 * h + 1] - bb.y, acc[4 * h + 2] - bb.z, acc[4 * h + 3] - bb.w);
     }
   } else if constexpr (W == 2) {
@@ -223,7 +337,7 @@ __device__ __forceinline__ void res_pack(const ChunkDev& C, int blk, float (*par
   if (q >= (C.nslices << C.cshift)) return;
   const int64_t sl = q >> C.cshift;
   const int lane = static_cast<int>(q & (C.C - 1));
-  slice_mm<W>(C.soff, C.val, C.col, sl, lane, C.C, C.Y, acc);
+  slice_mm<W>(C, C.soff, C.val, C.col, sl, lane, C.C, C.Y, acc);
   const int64_t row = slot_row_c(C.perm, C.nrows, q);
   if (row >= 0) store_residual<W>(C, row, acc);
 }
@@ -231,10 +345,10 @@ __device__ __forceinline__ void res_pack(const ChunkDev& C, int blk, float (*par
 __global__ __launch_bounds__(kBlock) void k_res_batched(const ChunkDev* __restrict__ ch, const int* __restrict__ first,
                                                         int nchunks, int* __restrict__ kdev) {
   if (blockIdx.x == 0 && threadIdx.x == 0) *kdev += 1;
-  const int c = chunk_of(first, nchunks, blockIdx.x);
-  const ChunkDev& C = ch[c];
+  const Place at = place_of(ch, first, nchunks);
+  const ChunkDev& C = ch[at.c];
   if (!C.act[kR]) return;  // every problem of this chunk has stopped
-  const int blk = blockIdx.x - first[c];
+  const int blk = at.blk;
   __shared__ float part[kWaves][kR][kWave];
   switch (C.W) {
     case 8: res_pack<8>(C, blk, part); break;
@@ -257,7 +371,7 @@ __device__ __forceinline__ void prox_pack(const ChunkDev& C, int blk, const int*
     if (q >= (C.nslicesT << C.cshift)) return;
     const int64_t sl = q >> C.cshift;
     const int lane = static_cast<int>(q & (C.C - 1));
-    slice_mm<W>(C.soffT, C.valT, C.colT, sl, lane, C.C, C.Rr, g);
+    slice_mm<W>(C, C.soffT, C.valT, C.colT, sl, lane, C.C, C.Rr, g);
     row = slot_row_c(C.permT, C.nrows, q);
   }
   if (row < 0) return;
@@ -266,15 +380,16 @@ __device__ __forceinline__ void prox_pack(const ChunkDev& C, int blk, const int*
   const float pi = C.pinv ? C.pinv[row] : 1.0f;
   // the row's W slots as whole vectors (a stopped problem's slots are written
   // back unchanged), so every store fills whole segments
-  float* X = C.X + row * W;
-  float* Y = C.Y + row * W;
-  const double* A = C.Anc + row * W;
+  const int64_t at = slot_of<W>(C, row, 0);
+  float* X = C.X + at;
+  float* Y = C.Y + at;
+  const double* A = C.Anc + at;
   float x[W], y[W];
   double a[W];
   if constexpr (W >= 4) {
 #pragma unroll
     for (int h = 0; h < W / 4; ++h) {
-      const float4 xv = reinterpret_cast<const float4*>(X)[h], yv = reinterpret_cast<const float4*>(Y)[h];
+      const float4 xv = *reinterpret_cast<const float4*>(X + h * C.half), yv = *reinterpret_cast<const float4*>(Y + h * C.half);
       x[4 * h] = xv.x; x[4 * h + 1] = xv.y; x[4 * h + 2] = xv.z; x[4 * h + 3] = xv.w;
       y[4 * h] = yv.x; y[4 * h + 1] = yv.y; y[4 * h + 2] = yv.z; y[4 * h + 3] = yv.w;
     }
@@ -289,7 +404,7 @@ __device__ __forceinline__ void prox_pack(const ChunkDev& C, int blk, const int*
   if constexpr (W >= 2) {
 #pragma unroll
     for (int h = 0; h < W / 2; ++h) {
-      const double2 av = reinterpret_cast<const double2*>(A)[h];
+      const double2 av = *reinterpret_cast<const double2*>(A + (h / 2) * C.half + 2 * (h % 2));
       a[2 * h] = av.x;
       a[2 * h + 1] = av.y;
     }
@@ -306,8 +421,8 @@ __device__ __forceinline__ void prox_pack(const ChunkDev& C, int blk, const int*
   if constexpr (W >= 4) {
 #pragma unroll
     for (int h = 0; h < W / 4; ++h) {
-      reinterpret_cast<float4*>(X)[h] = make_float4(x[4 * h], x[4 * h + 1], x[4 * h + 2], x[4 * h + 3]);
-      reinterpret_cast<float4*>(Y)[h] = make_float4(y[4 * h], y[4 * h + 1], y[4 * h + 2], y[4 * h + 3]);
+      *reinterpret_cast<float4*>(X + h * C.half) = make_float4(x[4 * h], x[4 * h + 1], x[4 * h + 2], x[4 * h + 3]);
+      *reinterpret_cast<float4*>(Y + h * C.half) = make_float4(y[4 * h], y[4 * h + 1], y[4 * h + 2], y[4 * h + 3]);
     }
   } else if constexpr (W == 2) {
     *reinterpret_cast<float2*>(X) = make_float2(x[0], x[1]);
@@ -320,10 +435,10 @@ __device__ __forceinline__ void prox_pack(const ChunkDev& C, int blk, const int*
 
 __global__ __launch_bounds__(kBlock) void k_prox_batched(const ChunkDev* __restrict__ ch, const int* __restrict__ first,
                                                          int nchunks, const int* __restrict__ kdev) {
-  const int c = chunk_of(first, nchunks, blockIdx.x);
-  const ChunkDev& C = ch[c];
+  const Place at = place_of(ch, first, nchunks);
+  const ChunkDev& C = ch[at.c];
   if (!C.act[kR]) return;  // every problem of this chunk has stopped
-  const int blk = blockIdx.x - first[c];
+  const int blk = at.blk;
   __shared__ float part[kWaves][kR][kWave];
   switch (C.W) {
     case 8: prox_pack<8>(C, blk, kdev, part); break;
@@ -368,23 +483,38 @@ __device__ __forceinline__ int tile_mm64(const ChunkDev& C, int m, int tile, con
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int row = tile_row(d, lane);
   const RowCode rc = tile_row_code(C.geo, d, row);
-  auto add = [&](int col, float w) {
-    const T* p = V + static_cast<int64_t>(col) * W;
+  const auto load = [&](int col, T (&x)[W]) {
 #pragma unroll
-    for (int j = 0; j < W; ++j) acc[j] = fma(static_cast<double>(w), static_cast<double>(p[j]), acc[j]);
+    for (int j = 0; j < W; ++j) x[j] = V[static_cast<int64_t>(col) * (W == 8 ? 4 : W) + (j >= 4 ? C.half : 0) + (j & 3)];
   };
-  for (int k = (d.x >> 2) + wv; k < (d.y >> 2); k += kWaves) {
-    uint4 c;
-    float4 v;
-    group_at(C, m, k, lane, c, v);
-    const int4 col = group_cols(C.geo, rc, c);
-    add(col.x, v.x);
-    add(col.y, v.y);
-    add(col.z, v.z);
-    add(col.w, v.w);
-  }
+  const auto add = [&](const T (&x)[W], float w) {
+#pragma unroll
+    for (int j = 0; j < W; ++j) acc[j] = fma(static_cast<double>(w), static_cast<double>(x[j]), acc[j]);
+  };
+  const auto cols = [&](int4& col, const uint4& c) { col = group_cols(C.geo, rc, c); };
+  const auto group = [&](const int4& col, const float4& v) {   // two columns' loads before their sums
+    T x[2][W];
+    load(col.x, x[0]);
+    load(col.y, x[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    add(x[0], v.x);
+    add(x[1], v.y);
+    load(col.z, x[0]);
+    load(col.w, x[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    add(x[0], v.z);
+    add(x[1], v.w);
+  };
+  if (C.tkept)
+    for_groups<true, int4>(C, m, (d.x >> 2) + wv, d.y >> 2, lane, cols, group);
+  else
+    for_groups<false, int4>(C, m, (d.x >> 2) + wv, d.y >> 2, lane, cols, group);
   if (row >= 0 && (d.w & kHasEsc))
-    for (int k = C.terp[m][row] + wv; k < C.terp[m][row + 1]; k += kWaves) add(C.tec[m][k], C.tev[m][k]);
+    for (int k = C.terp[m][row] + wv; k < C.terp[m][row + 1]; k += kWaves) {
+      T x[W];
+      load(C.tec[m][k], x);
+      add(x, C.tev[m][k]);
+    }
 #pragma unroll
   for (int j = 0; j < kR; ++j) part[wv][j][lane] = acc[j];
   __syncthreads();
@@ -402,7 +532,7 @@ __device__ __forceinline__ int tile_mm64(const ChunkDev& C, int m, int tile, con
 // Forward half of the float64 check on the anchors: r64 = Theta_K anchor - x0
 // and per-block sums of r^2, r.x0, |anchor| per right-hand side.
 template <int W>
-__device__ __forceinline__ void check_fwd_pack(const ChunkDev& C, int blk, double* __restrict__ part,
+__device__ __forceinline__ void check_fwd_pack(const ChunkDev& C, int blk, int slot, double* __restrict__ part,
                                                int64_t nblocks, double (*tpart)[kR][kWave]) {
   double a[kR], rr[kR], rb[kR], l1[kR];
 #pragma unroll
@@ -425,7 +555,7 @@ __device__ __forceinline__ void check_fwd_pack(const ChunkDev& C, int blk, doubl
         for (int t = 0; t < 4; ++t)
 #pragma unroll
           for (int j = 0; j < W; ++j)
-            a[j] = fma(static_cast<double>(vv[t]), C.Anc[static_cast<int64_t>(ci[t]) * W + j], a[j]);
+            a[j] = fma(static_cast<double>(vv[t]), C.Anc[slot_of<W>(C, ci[t], j)], a[j]);
       }
       row = slot_row_c(C.perm, C.nrows, q);
     }
@@ -433,40 +563,41 @@ __device__ __forceinline__ void check_fwd_pack(const ChunkDev& C, int blk, doubl
   if (row >= 0) {
 #pragma unroll
     for (int j = 0; j < W; ++j) {
-      const double b = static_cast<double>(C.X0[row * W + j]);
+      const int64_t at = slot_of<W>(C, row, j);
+      const double b = static_cast<double>(C.X0[at]);
       const double r = a[j] - b;
-      C.r64[row * W + j] = r;
+      C.r64[at] = r;
       rr[j] = r * r;
       rb[j] = r * b;
-      l1[j] = fabs(C.Anc[row * W + j]);
+      l1[j] = fabs(C.Anc[at]);
     }
   }
   double out[kR];
   block_reduce8(rr, false, out);
-  if (threadIdx.x < kR) part[(0 * kR + threadIdx.x) * nblocks + blockIdx.x] = out[threadIdx.x];
+  if (threadIdx.x < kR) part[(0 * kR + threadIdx.x) * nblocks + slot] = out[threadIdx.x];
   block_reduce8(rb, false, out);
-  if (threadIdx.x < kR) part[(1 * kR + threadIdx.x) * nblocks + blockIdx.x] = out[threadIdx.x];
+  if (threadIdx.x < kR) part[(1 * kR + threadIdx.x) * nblocks + slot] = out[threadIdx.x];
   block_reduce8(l1, false, out);
-  if (threadIdx.x < kR) part[(2 * kR + threadIdx.x) * nblocks + blockIdx.x] = out[threadIdx.x];
+  if (threadIdx.x < kR) part[(2 * kR + threadIdx.x) * nblocks + slot] = out[threadIdx.x];
 }
 
 __global__ __launch_bounds__(kBlock) void k_check_fwd(const ChunkDev* __restrict__ ch, const int* __restrict__ first,
                                                       int nchunks, double* __restrict__ part, int64_t nblocks) {
-  const int c = chunk_of(first, nchunks, blockIdx.x);
-  const ChunkDev& C = ch[c];
+  const Place at = place_of(ch, first, nchunks);
+  const ChunkDev& C = ch[at.c];
   if (!C.act[kR]) return;  // every problem of this chunk has stopped
-  const int blk = blockIdx.x - first[c];
+  const int blk = at.blk;
   __shared__ double tpart[kWaves][kR][kWave];
   switch (C.W) {
-    case 8: check_fwd_pack<8>(C, blk, part, nblocks, tpart); break;
-    case 4: check_fwd_pack<4>(C, blk, part, nblocks, tpart); break;
-    case 2: check_fwd_pack<2>(C, blk, part, nblocks, tpart); break;
-    default: check_fwd_pack<1>(C, blk, part, nblocks, tpart); break;
+    case 8: check_fwd_pack<8>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
+    case 4: check_fwd_pack<4>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
+    case 2: check_fwd_pack<2>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
+    default: check_fwd_pack<1>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
   }
 }
 
 template <int W>
-__device__ __forceinline__ void check_bwd_pack(const ChunkDev& C, int blk, double* __restrict__ part,
+__device__ __forceinline__ void check_bwd_pack(const ChunkDev& C, int blk, int slot, double* __restrict__ part,
                                                int64_t nblocks, double (*tpart)[kR][kWave]) {
   double g[kR];
 #pragma unroll
@@ -492,7 +623,7 @@ __device__ __forceinline__ void check_bwd_pack(const ChunkDev& C, int blk, doubl
         for (int t = 0; t < 4; ++t)
 #pragma unroll
           for (int j = 0; j < W; ++j)
-            g[j] = fma(static_cast<double>(vv[t]), C.r64[static_cast<int64_t>(ci[t]) * W + j], g[j]);
+            g[j] = fma(static_cast<double>(vv[t]), C.r64[slot_of<W>(C, ci[t], j)], g[j]);
       }
       if (slot_row_c(C.permT, C.nrows, q) < 0)
 #pragma unroll
@@ -503,21 +634,21 @@ __device__ __forceinline__ void check_bwd_pack(const ChunkDev& C, int blk, doubl
   for (int j = 0; j < kR; ++j) g[j] = fabs(g[j]);
   double out[kR];
   block_reduce8(g, true, out);
-  if (threadIdx.x < kR) part[(3 * kR + threadIdx.x) * nblocks + blockIdx.x] = out[threadIdx.x];
+  if (threadIdx.x < kR) part[(3 * kR + threadIdx.x) * nblocks + slot] = out[threadIdx.x];
 }
 
 __global__ __launch_bounds__(kBlock) void k_check_bwd(const ChunkDev* __restrict__ ch, const int* __restrict__ first,
                                                       int nchunks, double* __restrict__ part, int64_t nblocks) {
-  const int c = chunk_of(first, nchunks, blockIdx.x);
-  const ChunkDev& C = ch[c];
+  const Place at = place_of(ch, first, nchunks);
+  const ChunkDev& C = ch[at.c];
   if (!C.act[kR]) return;  // every problem of this chunk has stopped
-  const int blk = blockIdx.x - first[c];
+  const int blk = at.blk;
   __shared__ double tpart[kWaves][kR][kWave];
   switch (C.W) {
-    case 8: check_bwd_pack<8>(C, blk, part, nblocks, tpart); break;
-    case 4: check_bwd_pack<4>(C, blk, part, nblocks, tpart); break;
-    case 2: check_bwd_pack<2>(C, blk, part, nblocks, tpart); break;
-    default: check_bwd_pack<1>(C, blk, part, nblocks, tpart); break;
+    case 8: check_bwd_pack<8>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
+    case 4: check_bwd_pack<4>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
+    case 2: check_bwd_pack<2>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
+    default: check_bwd_pack<1>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
   }
 }
 
@@ -573,15 +704,17 @@ __global__ __launch_bounds__(kBlock) void k_check_reduce(const int* __restrict__
 struct Src8 {
   const float* p[kR];
 };
-__global__ void k_interleave8(Src8 src, float* __restrict__ dst, float* __restrict__ dst2, int64_t N, int W) {
+__global__ void k_interleave8(Src8 src, float* __restrict__ dst, float* __restrict__ dst2, int64_t N, int W,
+                              bool planes) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= N) return;
 #pragma unroll
   for (int j = 0; j < kR; ++j) {
     if (j >= W) break;
     const float v = src.p[j] ? src.p[j][i] : 0.0f;
-    dst[i * W + j] = v;
-    if (dst2) dst2[i * W + j] = v;
+    const int64_t at = slot_of(W, planes, N, i, j);
+    dst[at] = v;
+    if (dst2) dst2[at] = v;
   }
 }
 
@@ -590,14 +723,14 @@ struct Dst8 {
   float* p[kR];
   double* p64[kR];
 };
-__global__ void k_deinterleave8(const double* __restrict__ src, Dst8 dst, int W, int64_t N) {
+__global__ void k_deinterleave8(const double* __restrict__ src, Dst8 dst, int W, bool planes, int64_t N) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= N) return;
 #pragma unroll
   for (int j = 0; j < kR; ++j) {
     if (j >= W) break;
     if (!dst.p[j]) continue;   // slot left out
-    const double v = src[i * W + j];
+    const double v = src[slot_of(W, planes, N, i, j)];
     dst.p[j][i] = static_cast<float>(v);
     if (dst.p64[j]) dst.p64[j][i] = v;
   }
@@ -610,6 +743,7 @@ __global__ void k_deinterleave8(const double* __restrict__ src, Dst8 dst, int W,
 struct NarrowJob {
   int64_t off, N;
   int Wold, W;
+  bool planes;   // the old block's, where Wold = 8
   int from[kR];
   Dst8 out;
 };
@@ -621,7 +755,7 @@ __global__ void k_narrow_out(const NarrowJob* __restrict__ jobs, const double* _
        i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
     for (int j = 0; j < J.Wold; ++j) {
       if (!J.out.p[j]) continue;
-      const double v = anc[J.off + i * J.Wold + j];
+      const double v = anc[J.off + slot_of(J.Wold, J.planes, J.N, i, j)];
       J.out.p[j][i] = static_cast<float>(v);
       if (J.out.p64[j]) J.out.p64[j][i] = v;
     }
@@ -644,7 +778,7 @@ __global__ void k_narrow_move(const NarrowJob* __restrict__ jobs, const T* __res
   const NarrowJob& J = jobs[blockIdx.y];
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < J.N;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x)
-    for (int j = 0; j < J.W; ++j) dst[J.off + i * J.W + j] = tmp[J.off + i * J.Wold + J.from[j]];
+    for (int j = 0; j < J.W; ++j) dst[J.off + i * J.W + j] = tmp[J.off + slot_of(J.Wold, J.planes, J.N, i, J.from[j])];
 }
 
 __global__ void k_set(int* p, int v) { *p = v; }
@@ -711,6 +845,7 @@ extern "C" wdb_status wdb_solve_batched(int32_t nprob, const wdb_problem* probs,
       h.blocks_prox = static_cast<int>((th->At.nslices * th->At.C + kBlock - 1) / kBlock);
       h.blocks = std::max(h.blocks_res, h.blocks_prox);
       if (kernel_group(th) == kTiled) h.blocks = std::max<int>(h.blocks, static_cast<int>(th->tA.ntiles));
+      h.blocks = (h.blocks + 7) / 8 * 8;   // whole rounds of the XCDs
       chunks.push_back(std::move(h));
     }
   }
@@ -759,6 +894,9 @@ extern "C" wdb_status wdb_solve_batched(int32_t nprob, const wdb_problem* probs,
     d.Anc = pAnc.p + h.off;
     d.Rr = pRr.p + h.off;
     d.W = h.W;
+    d.g0 = c;
+    while (d.g0 > 0 && chunks[d.g0 - 1].th == th) --d.g0;
+    d.gn = static_cast<int>((members[th].size() + kR - 1) / kR);
     d.pinv = pre ? th->pinv : nullptr;
     d.tau = static_cast<float>(tau);
     d.act = pAct.p + static_cast<int64_t>(c) * (kR + 1);
@@ -784,6 +922,9 @@ extern "C" wdb_status wdb_solve_batched(int32_t nprob, const wdb_problem* probs,
         d.tev[m] = T[m]->ev;
       }
     }
+    const bool planes = d.ntiles > 0;
+    d.shift = planes ? 2 : 3;
+    d.half = planes ? 4 * N : 4;
     const Filter f = make_filter(th->wavelet);
     const size_t q = static_cast<size_t>(th->n / 2) * (th->n / 2);
     int* act = act_host.data() + static_cast<size_t>(c) * (kR + 1);
@@ -815,8 +956,8 @@ extern "C" wdb_status wdb_solve_batched(int32_t nprob, const wdb_problem* probs,
     if (nu) dwt_forward_many(th->n, th->levels, f, nu, us, xs, sa, sb, s);
     const dim3 g8(static_cast<unsigned>((N + 255) / 256));
     hipLaunchKernelGGL(k_interleave8, g8, dim3(256), 0, s, x0s, pX0.p + h.off, static_cast<float*>(nullptr), N,
-                       h.W);
-    hipLaunchKernelGGL(k_interleave8, g8, dim3(256), 0, s, inits, d.X, d.Y, N, h.W);
+                       h.W, planes);
+    hipLaunchKernelGGL(k_interleave8, g8, dim3(256), 0, s, inits, d.X, d.Y, N, h.W, planes);
     act[kR] = h.idx.empty() ? 0 : 1;
   }
   hipLaunchKernelGGL(k_anchor_init8, dim3(static_cast<unsigned>((tot8 + 255) / 256)), dim3(256), 0, s, pAnc.p, pCr.p,
@@ -929,6 +1070,7 @@ extern "C" wdb_status wdb_solve_batched(int32_t nprob, const wdb_problem* probs,
         J.N = h.th->N;
         J.Wold = h.W;
         J.W = Wn;
+        J.planes = hd[ci].ntiles > 0;
         for (int j = 0; j < kR; ++j) J.from[j] = j < static_cast<int>(keep.size()) ? keep[j] : 0;
         for (int j : drop) {
           J.out.p[j] = probs[h.idx[j]].x_out;
@@ -999,7 +1141,7 @@ extern "C" wdb_status wdb_solve_batched(int32_t nprob, const wdb_problem* probs,
       dst.p64[j] = probs[h.idx[j]].x64_out;
     }
     hipLaunchKernelGGL(k_deinterleave8, dim3(static_cast<unsigned>((N + 255) / 256)), dim3(256), 0, s,
-                       pAnc.p + h.off, dst, h.W, N);
+                       pAnc.p + h.off, dst, h.W, hd[ci].ntiles > 0, N);
   }
   WDB_HIP(hipGetLastError());
   WDB_HIP(hipStreamSynchronize(s));

@@ -1049,6 +1049,33 @@ def small32():
     return {"field": field, "h": h, "A": A, "A32": A32, "H": blur.blur_matrix(field)}
 
 
+@pytest.mark.parametrize("layout", ["sell", "dense", "kept"])
+def test_batched_packs_equal_packs_of_one(W, layout):
+    """Packs of 8, 4, 2 and 1 problems of two operators in one batch, their blocks
+    dealt in turns and padded to whole turns: every problem's iterate is that of
+    a batch of its own, to the last bit (the same sums in the same order)."""
+    ths = []
+    for n, J in ((32, 2), (64, 3)):
+        th = W.build_theta(synth.psf_rotating(n, 2.5, 1.0), "haar", J, 20 * n * n + 5)
+        th.lipschitz_lanczos()
+        if layout == "sell":
+            th.set_kernel_layout(16, 0)
+        else:
+            th.set_kernel_layout(8, 3)
+            th.set_tile_values(layout == "kept")
+        ths.append(th)
+    rng = np.random.default_rng(3)
+    probs = []
+    for i in range(8 + 4 + 10):   # 12 of the first operator (8 + 4), 10 of the second (8 + 2)
+        th = ths[0] if i < 12 else ths[1]
+        probs.append((th, dev(rng.random(th.N)), 1e-3 * (1 + i % 3)))
+    xs, infos = W.solve_batched(probs, 45, check_every=20)
+    for i, p in enumerate(probs):
+        x1, info1 = W.solve_batched([p], 45, check_every=20)
+        assert np.array_equal(host(xs[i]), host(x1[0])), i
+        assert abs(infos[i]["objective"] - info1[0]["objective"]) <= 1e-12 * info1[0]["objective"]
+
+
 @pytest.mark.parametrize("tiled", [False, True, "kept"])
 def test_batched_narrowing_keeps_the_iterates(W, p64, tiled):
     """A pack narrows (8 -> 4 -> 2 -> 1 slots) as its problems stop; that must
