@@ -21,7 +21,7 @@
 // W right-hand-side values (neighbouring lanes of a tile row read neighbouring
 // columns) and the tile value once for all of them.  Their float64 checks run
 // on the tiles too.  The gathers are bound by the L1's lines: their eight slots
-// lie in two planes [N][4], so that each 16-byte load of a tile row is whole
+// lie in two planes [N][4] (up to kDeepMax coefficients), so that each 16-byte load of a tile row is whole
 // lines, where [N][8] gives every load half of twice as many (24 problems of 256 x
 // 256, per iteration: 150 -> 129 us; with a group's operands under way while the one
 // before it is summed 129 -> 89 us, with the packs' order 89 -> 72 us).  What is
@@ -47,6 +47,14 @@ constexpr int kBlock = 128;   // 2 wavefronts per tile: 4% faster than 4 and 13%
 constexpr int kWave = 64;
 constexpr int kWaves = kBlock / kWave;
 constexpr int kR = 8;                  // right-hand sides per chunk
+// Largest problem of a batch that runs the kernels with operands a group ahead and,
+// on the tiles, slots in planes (DEEP).  Up to here an XCD's stripe of a vector is at
+// most a quarter of its L2 and the tiles' chains bound the launch; beyond, wavefronts
+// in flight count for more than the registers' worth of loads, and a run of columns
+// that begins within a line takes 4 lines in planes and 3 side by side (8 problems
+// of 1024 x 1024 per iteration: dense tiles 279 -> 242 us, kept 294 -> 239 us, sliced
+// ELL 329 -> 296 us; of 512 x 512, with the loads ahead: 85 -> 64, 117 -> 72, 128 -> 98).
+constexpr int64_t kDeepMax = 512 * 512;
 
 struct ChunkDev {
   const int64_t* soff;
@@ -164,13 +172,21 @@ struct Quad {
   }
 };
 
-template <int W>
+template <int W, bool DEEP>
 __device__ __forceinline__ void slice_mm(const ChunkDev& K, const int64_t* __restrict__ soff,
                                          const float4* __restrict__ val, const int4* __restrict__ col, int64_t sl,
                                          int lane, int C, const float* __restrict__ V, float (&acc)[kR]) {
   const int64_t end = soff[sl + 1] >> 2;
   int64_t j = (soff[sl] >> 2) + lane;
   if (j >= end) return;
+  if (!DEEP) {
+    for (; j < end; j += C) {
+      Quad<W> q;
+      q.template load<false>(K, V, col[j]);
+      q.add(val[j], acc);
+    }
+    return;
+  }
   // one quad's columns and the indices of the one after it are on their way while
   // a quad is summed
   float4 v = val[j], vn;
@@ -223,9 +239,21 @@ struct Group {
 // operands into an X, add(x, values) sums them.  The next group's operands and values
 // and the codes of the one after it are under way while a group is summed (a chain
 // of three loads a group otherwise: a tile's longest lists were most of an iteration).
-template <bool KEPT, typename X, typename LOAD, typename ADD>
+// Without DEEP a group's loads are left to it alone (fewer registers).
+template <bool KEPT, bool DEEP, typename X, typename LOAD, typename ADD>
 __device__ __forceinline__ void for_groups(const ChunkDev& C, int m, int k, int end, int lane, LOAD&& load, ADD&& add) {
   if (k >= end) return;
+  if (!DEEP) {
+    for (; k < end; k += kWaves) {
+      Group<KEPT> g;
+      X x;
+      g.codes(C, m, k, lane);
+      g.values(C, m);
+      load(x, g.r.code);
+      add(x, g.dense());
+    }
+    return;
+  }
   const int last = k + (end - 1 - k) / kWaves * kWaves;
   Group<KEPT> a, b;
   X xa, xb;
@@ -254,7 +282,7 @@ __device__ __forceinline__ void for_groups(const ChunkDev& C, int m, int k, int 
 // Tile `tile` of copy m (0: Theta_K, 1: Theta_K^T) times the [N][W] block V:
 // acc[0..W) of the lane's row, complete in wavefront 0 (the row's escapes
 // dealt to the wavefronts, whose partials are added in LDS in wavefront order).
-template <int W>
+template <int W, bool DEEP>
 __device__ __forceinline__ int tile_mm(const ChunkDev& C, int m, int tile, const float* __restrict__ V,
                                        float (&acc)[kR], float (*part)[kR][kWave]) {
   const int4 d = C.tdesc[m][tile];
@@ -262,12 +290,12 @@ __device__ __forceinline__ int tile_mm(const ChunkDev& C, int m, int tile, const
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int row = tile_row(d, lane);
   const RowCode rc = tile_row_code(C.geo, d, row);
-  const auto load = [&](Quad<W>& x, const uint4& c) { x.template load<true>(C, V, group_cols(C.geo, rc, c)); };
+  const auto load = [&](Quad<W>& x, const uint4& c) { x.template load<DEEP>(C, V, group_cols(C.geo, rc, c)); };
   const auto add = [&](const Quad<W>& x, const float4& v) { x.add(v, acc); };
   if (C.tkept)
-    for_groups<true, Quad<W>>(C, m, (d.x >> 2) + wv, d.y >> 2, lane, load, add);
+    for_groups<true, DEEP, Quad<W>>(C, m, (d.x >> 2) + wv, d.y >> 2, lane, load, add);
   else
-    for_groups<false, Quad<W>>(C, m, (d.x >> 2) + wv, d.y >> 2, lane, load, add);
+    for_groups<false, DEEP, Quad<W>>(C, m, (d.x >> 2) + wv, d.y >> 2, lane, load, add);
   if (row >= 0 && (d.w & kHasEsc)) {  // escapes dealt round-robin to the wavefronts, four in flight
     const int end = C.terp[m][row + 1];
     for (int k = C.terp[m][row] + wv; k < end; k += 4 * kWaves) {
@@ -279,7 +307,7 @@ __device__ __forceinline__ int tile_mm(const ChunkDev& C, int m, int tile, const
         w[t] = C.tev[m][min(k + t * kWaves, end - 1)];
       }
       Quad<W> x;
-      x.template load<true>(C, V, make_int4(c[0], c[1], c[2], c[3]));
+      x.template load<DEEP>(C, V, make_int4(c[0], c[1], c[2], c[3]));
 #pragma unroll
       for (int t = 0; t < 4; ++t)
         if (k + t * kWaves < end)
@@ -324,12 +352,12 @@ __device__ __forceinline__ void store_residual(const ChunkDev& C, int64_t row, c
   }
 }
 
-template <int W>
+template <int W, bool DEEP>
 __device__ __forceinline__ void res_pack(const ChunkDev& C, int blk, float (*part)[kR][kWave]) {
   float acc[kR] = {0, 0, 0, 0, 0, 0, 0, 0};
   if (C.ntiles) {
     if (blk >= C.ntiles) return;  // the chunk's block range also covers its sliced-ELL checks
-    const int row = tile_mm<W>(C, 0, blk, C.Y, acc, part);
+    const int row = tile_mm<W, DEEP>(C, 0, blk, C.Y, acc, part);
     if (row >= 0) store_residual<W>(C, row, acc);
     return;
   }
@@ -337,11 +365,12 @@ __device__ __forceinline__ void res_pack(const ChunkDev& C, int blk, float (*par
   if (q >= (C.nslices << C.cshift)) return;
   const int64_t sl = q >> C.cshift;
   const int lane = static_cast<int>(q & (C.C - 1));
-  slice_mm<W>(C, C.soff, C.val, C.col, sl, lane, C.C, C.Y, acc);
+  slice_mm<W, DEEP>(C, C.soff, C.val, C.col, sl, lane, C.C, C.Y, acc);
   const int64_t row = slot_row_c(C.perm, C.nrows, q);
   if (row >= 0) store_residual<W>(C, row, acc);
 }
 
+template <bool DEEP>
 __global__ __launch_bounds__(kBlock) void k_res_batched(const ChunkDev* __restrict__ ch, const int* __restrict__ first,
                                                         int nchunks, int* __restrict__ kdev) {
   if (blockIdx.x == 0 && threadIdx.x == 0) *kdev += 1;
@@ -351,27 +380,27 @@ __global__ __launch_bounds__(kBlock) void k_res_batched(const ChunkDev* __restri
   const int blk = at.blk;
   __shared__ float part[kWaves][kR][kWave];
   switch (C.W) {
-    case 8: res_pack<8>(C, blk, part); break;
-    case 4: res_pack<4>(C, blk, part); break;
-    case 2: res_pack<2>(C, blk, part); break;
-    default: res_pack<1>(C, blk, part); break;
+    case 8: res_pack<8, DEEP>(C, blk, part); break;
+    case 4: res_pack<4, DEEP>(C, blk, part); break;
+    case 2: res_pack<2, DEEP>(C, blk, part); break;
+    default: res_pack<1, DEEP>(C, blk, part); break;
   }
 }
 
-template <int W>
+template <int W, bool DEEP>
 __device__ __forceinline__ void prox_pack(const ChunkDev& C, int blk, const int* __restrict__ kdev,
                                           float (*part)[kR][kWave]) {
   float g[kR] = {0, 0, 0, 0, 0, 0, 0, 0};
   int64_t row;
   if (C.ntiles) {
     if (blk >= C.ntiles) return;
-    row = tile_mm<W>(C, 1, blk, C.Rr, g, part);
+    row = tile_mm<W, DEEP>(C, 1, blk, C.Rr, g, part);
   } else {
     const int64_t q = static_cast<int64_t>(blk) * kBlock + threadIdx.x;
     if (q >= (C.nslicesT << C.cshift)) return;
     const int64_t sl = q >> C.cshift;
     const int lane = static_cast<int>(q & (C.C - 1));
-    slice_mm<W>(C, C.soffT, C.valT, C.colT, sl, lane, C.C, C.Rr, g);
+    slice_mm<W, DEEP>(C, C.soffT, C.valT, C.colT, sl, lane, C.C, C.Rr, g);
     row = slot_row_c(C.permT, C.nrows, q);
   }
   if (row < 0) return;
@@ -433,6 +462,7 @@ __device__ __forceinline__ void prox_pack(const ChunkDev& C, int blk, const int*
   }
 }
 
+template <bool DEEP>
 __global__ __launch_bounds__(kBlock) void k_prox_batched(const ChunkDev* __restrict__ ch, const int* __restrict__ first,
                                                          int nchunks, const int* __restrict__ kdev) {
   const Place at = place_of(ch, first, nchunks);
@@ -441,10 +471,10 @@ __global__ __launch_bounds__(kBlock) void k_prox_batched(const ChunkDev* __restr
   const int blk = at.blk;
   __shared__ float part[kWaves][kR][kWave];
   switch (C.W) {
-    case 8: prox_pack<8>(C, blk, kdev, part); break;
-    case 4: prox_pack<4>(C, blk, kdev, part); break;
-    case 2: prox_pack<2>(C, blk, kdev, part); break;
-    default: prox_pack<1>(C, blk, kdev, part); break;
+    case 8: prox_pack<8, DEEP>(C, blk, kdev, part); break;
+    case 4: prox_pack<4, DEEP>(C, blk, kdev, part); break;
+    case 2: prox_pack<2, DEEP>(C, blk, kdev, part); break;
+    default: prox_pack<1, DEEP>(C, blk, kdev, part); break;
   }
 }
 
@@ -475,7 +505,7 @@ __device__ __forceinline__ void block_reduce8(double (&v)[kR], bool is_max, doub
 // float32 widened): acc[8] of the lane's row, complete in wavefront 0 (escapes
 // dealt to the four wavefronts; partials added in LDS in wavefront order).
 // Called by every thread of the block.
-template <int W, typename T>
+template <int W, bool DEEP, typename T>
 __device__ __forceinline__ int tile_mm64(const ChunkDev& C, int m, int tile, const T* __restrict__ V,
                                          double (&acc)[kR], double (*part)[kR][kWave]) {
   const int4 d = C.tdesc[m][tile];
@@ -485,7 +515,8 @@ __device__ __forceinline__ int tile_mm64(const ChunkDev& C, int m, int tile, con
   const RowCode rc = tile_row_code(C.geo, d, row);
   const auto load = [&](int col, T (&x)[W]) {
 #pragma unroll
-    for (int j = 0; j < W; ++j) x[j] = V[static_cast<int64_t>(col) * (W == 8 ? 4 : W) + (j >= 4 ? C.half : 0) + (j & 3)];
+    for (int j = 0; j < W; ++j)
+      x[j] = V[static_cast<int64_t>(col) * (DEEP && W == 8 ? 4 : W) + (DEEP && j >= 4 ? C.half + j - 4 : j)];
   };
   const auto add = [&](const T (&x)[W], float w) {
 #pragma unroll
@@ -496,19 +527,19 @@ __device__ __forceinline__ int tile_mm64(const ChunkDev& C, int m, int tile, con
     T x[2][W];
     load(col.x, x[0]);
     load(col.y, x[1]);
-    __builtin_amdgcn_sched_barrier(0);
+    if (DEEP) __builtin_amdgcn_sched_barrier(0);
     add(x[0], v.x);
     add(x[1], v.y);
     load(col.z, x[0]);
     load(col.w, x[1]);
-    __builtin_amdgcn_sched_barrier(0);
+    if (DEEP) __builtin_amdgcn_sched_barrier(0);
     add(x[0], v.z);
     add(x[1], v.w);
   };
   if (C.tkept)
-    for_groups<true, int4>(C, m, (d.x >> 2) + wv, d.y >> 2, lane, cols, group);
+    for_groups<true, DEEP, int4>(C, m, (d.x >> 2) + wv, d.y >> 2, lane, cols, group);
   else
-    for_groups<false, int4>(C, m, (d.x >> 2) + wv, d.y >> 2, lane, cols, group);
+    for_groups<false, DEEP, int4>(C, m, (d.x >> 2) + wv, d.y >> 2, lane, cols, group);
   if (row >= 0 && (d.w & kHasEsc))
     for (int k = C.terp[m][row] + wv; k < C.terp[m][row + 1]; k += kWaves) {
       T x[W];
@@ -531,7 +562,7 @@ __device__ __forceinline__ int tile_mm64(const ChunkDev& C, int m, int tile, con
 
 // Forward half of the float64 check on the anchors: r64 = Theta_K anchor - x0
 // and per-block sums of r^2, r.x0, |anchor| per right-hand side.
-template <int W>
+template <int W, bool DEEP>
 __device__ __forceinline__ void check_fwd_pack(const ChunkDev& C, int blk, int slot, double* __restrict__ part,
                                                int64_t nblocks, double (*tpart)[kR][kWave]) {
   double a[kR], rr[kR], rb[kR], l1[kR];
@@ -539,7 +570,7 @@ __device__ __forceinline__ void check_fwd_pack(const ChunkDev& C, int blk, int s
   for (int j = 0; j < kR; ++j) a[j] = rr[j] = rb[j] = l1[j] = 0.0;
   int64_t row = -1;
   if (C.ntiles) {
-    if (blk < C.ntiles) row = tile_mm64<W>(C, 0, blk, C.Anc, a, tpart);
+    if (blk < C.ntiles) row = tile_mm64<W, DEEP>(C, 0, blk, C.Anc, a, tpart);
   } else {
     const int64_t q = static_cast<int64_t>(blk) * kBlock + threadIdx.x;
     const int64_t sl = q >> C.cshift;
@@ -555,7 +586,7 @@ __device__ __forceinline__ void check_fwd_pack(const ChunkDev& C, int blk, int s
         for (int t = 0; t < 4; ++t)
 #pragma unroll
           for (int j = 0; j < W; ++j)
-            a[j] = fma(static_cast<double>(vv[t]), C.Anc[slot_of<W>(C, ci[t], j)], a[j]);
+            a[j] = fma(static_cast<double>(vv[t]), C.Anc[static_cast<int64_t>(ci[t]) * W + j], a[j]);
       }
       row = slot_row_c(C.perm, C.nrows, q);
     }
@@ -581,6 +612,7 @@ __device__ __forceinline__ void check_fwd_pack(const ChunkDev& C, int blk, int s
   if (threadIdx.x < kR) part[(2 * kR + threadIdx.x) * nblocks + slot] = out[threadIdx.x];
 }
 
+template <bool DEEP>
 __global__ __launch_bounds__(kBlock) void k_check_fwd(const ChunkDev* __restrict__ ch, const int* __restrict__ first,
                                                       int nchunks, double* __restrict__ part, int64_t nblocks) {
   const Place at = place_of(ch, first, nchunks);
@@ -589,14 +621,14 @@ __global__ __launch_bounds__(kBlock) void k_check_fwd(const ChunkDev* __restrict
   const int blk = at.blk;
   __shared__ double tpart[kWaves][kR][kWave];
   switch (C.W) {
-    case 8: check_fwd_pack<8>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
-    case 4: check_fwd_pack<4>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
-    case 2: check_fwd_pack<2>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
-    default: check_fwd_pack<1>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
+    case 8: check_fwd_pack<8, DEEP>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
+    case 4: check_fwd_pack<4, DEEP>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
+    case 2: check_fwd_pack<2, DEEP>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
+    default: check_fwd_pack<1, DEEP>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
   }
 }
 
-template <int W>
+template <int W, bool DEEP>
 __device__ __forceinline__ void check_bwd_pack(const ChunkDev& C, int blk, int slot, double* __restrict__ part,
                                                int64_t nblocks, double (*tpart)[kR][kWave]) {
   double g[kR];
@@ -604,7 +636,7 @@ __device__ __forceinline__ void check_bwd_pack(const ChunkDev& C, int blk, int s
   for (int j = 0; j < kR; ++j) g[j] = 0.0;
   if (C.ntiles) {
     int row = -1;
-    if (blk < C.ntiles) row = tile_mm64<W>(C, 1, blk, static_cast<const double*>(C.r64), g, tpart);
+    if (blk < C.ntiles) row = tile_mm64<W, DEEP>(C, 1, blk, static_cast<const double*>(C.r64), g, tpart);
     if (row < 0)
 #pragma unroll
       for (int j = 0; j < kR; ++j) g[j] = 0.0;
@@ -623,7 +655,7 @@ __device__ __forceinline__ void check_bwd_pack(const ChunkDev& C, int blk, int s
         for (int t = 0; t < 4; ++t)
 #pragma unroll
           for (int j = 0; j < W; ++j)
-            g[j] = fma(static_cast<double>(vv[t]), C.r64[slot_of<W>(C, ci[t], j)], g[j]);
+            g[j] = fma(static_cast<double>(vv[t]), C.r64[static_cast<int64_t>(ci[t]) * W + j], g[j]);
       }
       if (slot_row_c(C.permT, C.nrows, q) < 0)
 #pragma unroll
@@ -637,6 +669,7 @@ __device__ __forceinline__ void check_bwd_pack(const ChunkDev& C, int blk, int s
   if (threadIdx.x < kR) part[(3 * kR + threadIdx.x) * nblocks + slot] = out[threadIdx.x];
 }
 
+template <bool DEEP>
 __global__ __launch_bounds__(kBlock) void k_check_bwd(const ChunkDev* __restrict__ ch, const int* __restrict__ first,
                                                       int nchunks, double* __restrict__ part, int64_t nblocks) {
   const Place at = place_of(ch, first, nchunks);
@@ -645,10 +678,10 @@ __global__ __launch_bounds__(kBlock) void k_check_bwd(const ChunkDev* __restrict
   const int blk = at.blk;
   __shared__ double tpart[kWaves][kR][kWave];
   switch (C.W) {
-    case 8: check_bwd_pack<8>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
-    case 4: check_bwd_pack<4>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
-    case 2: check_bwd_pack<2>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
-    default: check_bwd_pack<1>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
+    case 8: check_bwd_pack<8, DEEP>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
+    case 4: check_bwd_pack<4, DEEP>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
+    case 2: check_bwd_pack<2, DEEP>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
+    default: check_bwd_pack<1, DEEP>(C, blk, first[at.c] + blk, part, nblocks, tpart); break;
   }
 }
 
@@ -850,6 +883,8 @@ extern "C" wdb_status wdb_solve_batched(int32_t nprob, const wdb_problem* probs,
     }
   }
   const int nch = static_cast<int>(chunks.size());
+  bool deep = true;
+  for (const Host& h : chunks) deep &= h.th->N <= kDeepMax;
   DevBuf<float> pX(tot8), pY(tot8), pX0(tot8), pRr(tot8), pCr(tot8);
   DevBuf<double> pR64(tot8), pAnc(tot8);
   DevBuf<int> pAct(static_cast<size_t>(nch) * (kR + 1));
@@ -922,7 +957,7 @@ extern "C" wdb_status wdb_solve_batched(int32_t nprob, const wdb_problem* probs,
         d.tev[m] = T[m]->ev;
       }
     }
-    const bool planes = d.ntiles > 0;
+    const bool planes = d.ntiles > 0 && deep;
     d.shift = planes ? 2 : 3;
     d.half = planes ? 4 * N : 4;
     const Filter f = make_filter(th->wavelet);
@@ -970,10 +1005,14 @@ extern "C" wdb_status wdb_solve_batched(int32_t nprob, const wdb_problem* probs,
   hipLaunchKernelGGL(k_set, dim3(1), dim3(1), 0, s, kdev.p, k0 - 1);
 
   auto iterate = [&](hipStream_t st) {
-    hipLaunchKernelGGL(k_res_batched, dim3(static_cast<unsigned>(nblocks)), dim3(kBlock), 0, st, dch.p, dfirst.p, nch,
-                       kdev.p);
-    hipLaunchKernelGGL(k_prox_batched, dim3(static_cast<unsigned>(nblocks)), dim3(kBlock), 0, st, dch.p, dfirst.p,
-                       nch, kdev.p);
+    const dim3 grid(static_cast<unsigned>(nblocks));
+    if (deep) {
+      hipLaunchKernelGGL(k_res_batched<true>, grid, dim3(kBlock), 0, st, dch.p, dfirst.p, nch, kdev.p);
+      hipLaunchKernelGGL(k_prox_batched<true>, grid, dim3(kBlock), 0, st, dch.p, dfirst.p, nch, kdev.p);
+    } else {
+      hipLaunchKernelGGL(k_res_batched<false>, grid, dim3(kBlock), 0, st, dch.p, dfirst.p, nch, kdev.p);
+      hipLaunchKernelGGL(k_prox_batched<false>, grid, dim3(kBlock), 0, st, dch.p, dfirst.p, nch, kdev.p);
+    }
   };
   const int c = opts->check_every;
   const int total = opts->max_iters;
@@ -1007,10 +1046,10 @@ extern "C" wdb_status wdb_solve_batched(int32_t nprob, const wdb_problem* probs,
       if (!at_check) continue;
       const dim3 gall(static_cast<unsigned>((tot8 + 255) / 256));
       hipLaunchKernelGGL(k_reanchor8, gall, dim3(256), 0, s, pAnc.p, pX.p, pY.p, tot8);
-      hipLaunchKernelGGL(k_check_fwd, dim3(static_cast<unsigned>(nblocks)), dim3(kBlock), 0, s, dch.p, dfirst.p, nch,
-                         part.p, nblocks);
-      hipLaunchKernelGGL(k_check_bwd, dim3(static_cast<unsigned>(nblocks)), dim3(kBlock), 0, s, dch.p, dfirst.p, nch,
-                         part.p, nblocks);
+      hipLaunchKernelGGL(deep ? k_check_fwd<true> : k_check_fwd<false>, dim3(static_cast<unsigned>(nblocks)),
+                         dim3(kBlock), 0, s, dch.p, dfirst.p, nch, part.p, nblocks);
+      hipLaunchKernelGGL(deep ? k_check_bwd<true> : k_check_bwd<false>, dim3(static_cast<unsigned>(nblocks)),
+                         dim3(kBlock), 0, s, dch.p, dfirst.p, nch, part.p, nblocks);
       hipLaunchKernelGGL(k_check_reduce, dim3(nch * 4 * kR), dim3(kBlock), 0, s, dfirst.p, part.p, nblocks, red.p);
       hipLaunchKernelGGL(k_anchor_rhs8, gall, dim3(256), 0, s, pR64.p, pCr.p, tot8);
       WDB_HIP(hipGetLastError());
@@ -1070,7 +1109,7 @@ extern "C" wdb_status wdb_solve_batched(int32_t nprob, const wdb_problem* probs,
         J.N = h.th->N;
         J.Wold = h.W;
         J.W = Wn;
-        J.planes = hd[ci].ntiles > 0;
+        J.planes = hd[ci].shift == 2;
         for (int j = 0; j < kR; ++j) J.from[j] = j < static_cast<int>(keep.size()) ? keep[j] : 0;
         for (int j : drop) {
           J.out.p[j] = probs[h.idx[j]].x_out;
@@ -1141,7 +1180,7 @@ extern "C" wdb_status wdb_solve_batched(int32_t nprob, const wdb_problem* probs,
       dst.p64[j] = probs[h.idx[j]].x64_out;
     }
     hipLaunchKernelGGL(k_deinterleave8, dim3(static_cast<unsigned>((N + 255) / 256)), dim3(256), 0, s,
-                       pAnc.p + h.off, dst, h.W, hd[ci].ntiles > 0, N);
+                       pAnc.p + h.off, dst, h.W, hd[ci].shift == 2, N);
   }
   WDB_HIP(hipGetLastError());
   WDB_HIP(hipStreamSynchronize(s));

@@ -1076,6 +1076,37 @@ def test_batched_packs_equal_packs_of_one(W, layout):
         assert abs(infos[i]["objective"] - info1[0]["objective"]) <= 1e-12 * info1[0]["objective"]
 
 
+@pytest.mark.parametrize("layout", ["sell", "dense", "kept"])
+def test_batched_with_a_large_operator_keeps_the_iterates(W, layout):
+    """A batch that holds a problem of more than 512 x 512 coefficients runs the
+    kernels without loads ahead and planes: the small problems' iterates stay
+    those of a batch of their own, to the last bit, and the large one (the
+    identity, for which Alg. 1 thresholds x0 in its first step) is exact."""
+    n = 1024
+    N = n * n
+    one = W.Theta.from_csr(n, "haar", 1, np.arange(N + 1, dtype=np.int64), np.arange(N, dtype=np.int32), np.ones(N))
+    one.lipschitz_lanczos()
+    th = W.build_theta(synth.psf_rotating(64, 2.5, 1.0), "haar", 3, 20 * 4096 + 5)
+    th.lipschitz_lanczos()
+    for t in (one, th):
+        if layout == "sell":
+            t.set_kernel_layout(16, 0)
+        else:
+            t.set_kernel_layout(8, 3)
+            t.set_tile_values(layout == "kept")
+    rng = np.random.default_rng(5)
+    small = [(th, dev(rng.standard_normal(4096)), 1e-3 * (1 + i)) for i in range(6)]
+    big = (one, dev(rng.standard_normal(N)), 0.5)
+    xs, infos = W.solve_batched(small[:3] + [big] + small[3:], 45, check_every=20, coeffs=True)
+    alone, inf1 = W.solve_batched(small, 45, check_every=20, coeffs=True)
+    for i, (x, info) in enumerate(zip(xs[:3] + xs[4:], infos[:3] + infos[4:])):
+        assert np.array_equal(host(x), host(alone[i])), i
+        assert abs(info["objective"] - inf1[i]["objective"]) <= 1e-12 * inf1[i]["objective"]
+    x0 = host(big[1])
+    # tau = 1 / L and L = 1 to 1e-12: float32 rounding of the step alone
+    assert np.max(np.abs(host(xs[3]) - np.sign(x0) * np.maximum(np.abs(x0) - 0.5, 0.0))) <= 2e-6
+
+
 @pytest.mark.parametrize("tiled", [False, True, "kept"])
 def test_batched_narrowing_keeps_the_iterates(W, p64, tiled):
     """A pack narrows (8 -> 4 -> 2 -> 1 slots) as its problems stop; that must
