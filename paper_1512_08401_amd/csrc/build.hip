@@ -467,9 +467,16 @@ struct Builder {
     const size_t entry = 2 * sizeof(int32_t) + sizeof(double);
     const size_t kept = (static_cast<size_t>(nnz_budget) + kBoundaryCap) * entry;
     if (free < kept || static_cast<size_t>(span * span * N) > (free - kept) / 4 / sizeof(double)) return;
-    wt.alloc(span * span * N);
     T.tiles = (G.n + kReach - 1) / kReach;
-    reach.alloc(static_cast<size_t>(span) * T.tiles * T.tiles);
+    try {
+      wt.alloc(span * span * N);
+      reach.alloc(static_cast<size_t>(span) * T.tiles * T.tiles);
+    } catch (...) {   // taken meanwhile (another thread's build)
+      (void)hipGetLastError();
+      wt.reset();
+      reach.reset();
+      return;
+    }
     T.wt = wt.p;
     T.reach = reach.p;
     hipLaunchKernelGGL(k_weights, dim3(static_cast<unsigned>((N + 255) / 256), static_cast<unsigned>(span)), dim3(256),
