@@ -410,15 +410,20 @@ void with_taps(int L, F&& f) {
   }
 }
 
-// Launches with more than 64 KiB of LDS need the kernel's limit raised, once
-// per device (`done`: a bit per device).
+// Dynamic LDS that a block of any of these kernels may take: what is left beside
+// k_dwt_inv's intervals (the runtime refuses a limit that does not fit with them).
+constexpr size_t kDynLds = 160 * 1024 - sizeof(int4) * (kMaxLevels + 1);
+
+// Launches with more than 64 KiB of LDS (on the inverse: 12 taps from 6 levels
+// on, 8 taps from 10) need the kernel's limit raised, once per device (`done`: a
+// bit per device).
 void raise_lds(const void* kernel, size_t bytes, std::atomic<uint64_t>& done) {
   if (bytes <= 64 * 1024) return;
   int dev = 0;
   WDB_HIP(hipGetDevice(&dev));
   const uint64_t bit = uint64_t{1} << (dev & 63);
   if (done.load() & bit) return;
-  WDB_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+  WDB_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kDynLds));
   done.fetch_or(bit);
 }
 
@@ -526,7 +531,7 @@ void dwt_inverse_many(int n, int levels, const Filter& f, int count, const float
     pl.ll = at;
     pl.rows = at + big;
     const size_t bytes = (pl.rows + 2 * static_cast<size_t>(most)) * sizeof(float);
-    WDB_REQUIRE(bytes <= 160 * 1024, WDB_ERR_LEVELS, "the inverse transform's levels do not fit on chip");
+    WDB_REQUIRE(bytes <= kDynLds, WDB_ERR_LEVELS, "the inverse transform's levels do not fit on chip");
     for (int b0 = 0; b0 < count; b0 += kBatch) {
       const int nb = std::min(kBatch, count - b0);
       InvPtrs P{};

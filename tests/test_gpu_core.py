@@ -107,6 +107,19 @@ def test_dwt_launch_plans_match_oracle(W, name, n, J):
     assert np.array_equal(v, host(W.dwt(dev(c), name, J, inverse=True)))
 
 
+@pytest.mark.parametrize("name,n,J,count", [("sym6", 512, 6, 5), ("sym6", 1024, 6, 1), ("sym6", 2048, 8, 1),
+                                            ("db4", 4096, 10, 1)])
+def test_inverse_dwt_of_many_levels_matches_oracle(W, name, n, J, count):
+    """Inverse transforms whose levels take more than 64 KiB of LDS (the fewest and
+    the most levels of 12 taps, the fewest of 8).  Bar of the tests above."""
+    print(f"idwt {name} n={n} J={J} count={count}", flush=True)
+    c = np.random.default_rng(n + J).standard_normal((count, n * n)).astype(np.float32)
+    v = host(W.dwt_batched(dev(c), name, J, inverse=True)).reshape(count, -1)
+    for i in {0, count - 1}:
+        vo = dwt.idwt2(c[i].astype(np.float64), filters.by_name(name), J, n).ravel()
+        assert np.max(np.abs(v[i] - vo)) <= 2e-6 * np.max(np.abs(vo))
+
+
 def test_dwt_many_images_match_single(W):
     """More images than a launch takes, and enough blocks for the larger tile."""
     n, J, count = 64, 2, 261
