@@ -121,9 +121,9 @@ __device__ __forceinline__ double fma_const(double a, double b, double c) {
   return d;
 }
 
-// 2^-x for x >= 0: -x = n + r, |r| <= 1/2, and the Taylor polynomial of degree
-// 13 of 2^r (its remainder is below 5e-18) times 2^n.  n comes from the low bits
-// of a sum with 1.5 * 2^52.
+// 2^-x for 0 <= x < 2^31: -x = n + r, |r| <= 1/2, and the Taylor polynomial of
+// degree 13 of 2^r (its remainder is below 5e-18) times 2^n.  n comes from the
+// low 32 bits of a sum with 1.5 * 2^52.
 __device__ __forceinline__ double exp2_neg(double x) {
   constexpr double kShift = 6755399441055744.0, kLn2 = 0.6931471805599453;
   const double t = kShift - x;
@@ -356,10 +356,16 @@ __global__ void k_exact_init(const float* __restrict__ src, float* __restrict__ 
 
 dim3 pix_grid(int64_t N) { return dim3(static_cast<unsigned>((N + 255) / 256)); }
 
+// Largest scaled q whose weight 2^-q is not 0 in float64.
+constexpr double kLeast = 1074.0;
+
+// A cut-off beyond kLeast (any trunc above 38.6) is brought down to it: the same
+// sums, and exp2_neg's argument stays in its range (q reaches trunc^2).
 ExDev view(const wdb_exact* ex) {
   const double T2 = ex->F.trunc * ex->F.trunc;
   const double k2 = kScale * kScale;
-  return ExDev{ex->F.dev(), ex->coef.p, ex->reach.p, ex->ntile, k2 * (T2 - ex->near), k2 * (T2 + ex->near)};
+  return ExDev{ex->F.dev(), ex->coef.p, ex->reach.p, ex->ntile, std::min(k2 * (T2 - ex->near), kLeast),
+               std::min(k2 * (T2 + ex->near), kLeast)};
 }
 
 // f(TH): 32 x 32 targets per block where those fill the chip, else 32 x 8 with four

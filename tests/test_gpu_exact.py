@@ -3,6 +3,8 @@ Sec. 5): H and H^* of the PSF field against the oracle's blur matrix, the
 Lipschitz constant against the dense spectral norm, and Alg. 1 with the
 exact gradient Psi^* H^* (H Psi y - u0) against the oracle's Alg. 1 on the
 whole (untruncated) Theta = Psi^* H Psi."""
+import types
+
 import numpy as np
 import pytest
 import scipy.sparse as sp
@@ -135,3 +137,23 @@ def test_exact_launches_match_direct_sums(W, field):
     one[n + 1] = 1.0
     seen = direct_products(field, one, one)[0] != 0
     assert np.array_equal(~np.isfinite(host(ex.apply(dev(u)))), seen)
+
+
+@pytest.mark.parametrize("n,sigma,trunc", [(64, 5e-4, 6e4), (64, 0.5, 60.0)])
+def test_exact_weights_far_past_underflow_are_zero(W, n, sigma, trunc):
+    """Cut-offs whose ellipse reaches far beyond the weights that float64 can
+    hold: those are 0, and the products are finite.  With sigma 5e-4 the quadratic form
+    passes 2^31 and every PSF is its own pixel.  Bar of the test above."""
+    full = lambda v: np.full(n * n, v)
+    field = types.SimpleNamespace(n=n, sig_major=full(sigma), sig_minor=full(sigma), angle=full(0.3), trunc=trunc)
+    print(f"exact sigma={sigma} trunc={trunc}", flush=True)
+    u = np.random.default_rng(n).standard_normal(n * n).astype(np.float32)
+    Hu, Hv = direct_products(field, u, u)
+    ex = W.Exact(field, "haar", 1)
+    assert np.max(np.abs(host(ex.apply(dev(u))) - Hu)) <= 1e-7 * np.max(np.abs(Hu))
+    assert np.max(np.abs(host(ex.apply(dev(u), adjoint=True)) - Hv)) <= 1e-7 * np.max(np.abs(Hv))
+    if sigma < 0.01:
+        assert np.array_equal(Hu, u)
+        u[5] = np.inf
+        for adjoint in (False, True):
+            assert np.flatnonzero(~np.isfinite(host(ex.apply(dev(u), adjoint=adjoint)))).tolist() == [5]
