@@ -77,6 +77,12 @@ __global__ __launch_bounds__(256) void k_exact_coef(PsfDev P, double* __restrict
   coef[2 * N + s] = kScale * c / b;
   coef[3 * N + s] = kScale * sn / b;
   coef[4 * N + s] = 1.0 / P.Z[s];
+  // a PSF without weights (the squares of its sigmas underflow, so that not even its
+  // centre is inside): a NaN is never inside either
+  if (!(P.Z[s] > 0.0)) {
+    for (int k = 0; k < 4; ++k) coef[k * N + s] = __longlong_as_double(0x7ff8000000000000ll);
+    coef[4 * N + s] = 0.0;
+  }
 }
 
 // Reach of a tile of sources (blockIdx.x), thread = source.

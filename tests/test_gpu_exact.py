@@ -157,3 +157,21 @@ def test_exact_weights_far_past_underflow_are_zero(W, n, sigma, trunc):
         u[5] = np.inf
         for adjoint in (False, True):
             assert np.flatnonzero(~np.isfinite(host(ex.apply(dev(u), adjoint=adjoint)))).tolist() == [5]
+
+
+def test_exact_sources_without_weights_spread_nothing(W):
+    """Sources whose squared sigmas underflow have an empty PSF: their pixels, even
+    infinite ones, reach no target, and H^* is 0 at them."""
+    n = 16
+    field = synth.psf_rotating(n, 1.5, 0.8)
+    none = np.random.default_rng(0).random(n * n) < 0.3
+    u = np.random.default_rng(1).standard_normal(n * n).astype(np.float32)
+    Hu, Hv = direct_products(field, np.where(none, 0.0, u), u)
+    for sig in (field.sig_major, field.sig_minor):
+        sig.reshape(-1)[none] = 1e-170
+    ex = W.Exact(field, "haar", 1)
+    v = host(ex.apply(dev(u), adjoint=True))
+    assert np.all(v[none] == 0.0)
+    assert np.max(np.abs(v - np.where(none, 0.0, Hv))) <= 1e-7 * np.max(np.abs(Hv))
+    u[none] = np.inf
+    assert np.max(np.abs(host(ex.apply(dev(u))) - Hu)) <= 1e-7 * np.max(np.abs(Hu))
