@@ -214,8 +214,8 @@ __device__ __forceinline__ void fwd_stack(const StackArg& S, const float* __rest
     b1[j] = bf2f(S.b[0][drow(j, hi)]);
     b2[j] = bf2f(S.b[1][drow(j, hi)]);
   }
-  // byte offsets of this lane half's two taps of each conv1 step (the weights
-  // of taps above 8 are zero)
+  // byte offsets of this lane half's two taps of each conv1 step (taps above 8:
+  // zero weights and, for an infinite input's sake, zero operands)
   int zo[3][2];
 #pragma unroll
   for (int k = 0; k < 3; ++k)
@@ -275,8 +275,10 @@ __device__ __forceinline__ void fwd_stack(const StackArg& S, const float* __rest
       for (int p = 2; p >= 0; --p)
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-          const u32x2 a = *reinterpret_cast<const u32x2*>(zp + p * kZPlane + zo[k][0]);
-          const u32x2 c = *reinterpret_cast<const u32x2*>(zp + p * kZPlane + zo[k][1]);
+          u32x2 a = *reinterpret_cast<const u32x2*>(zp + p * kZPlane + zo[k][0]);
+          u32x2 c = {0, 0};
+          if (k < 2) c = *reinterpret_cast<const u32x2*>(zp + p * kZPlane + zo[k][1]);
+          else if (hi) a = u32x2{0, 0};
           acc = mma(w1[k], u32x4{a.x, a.y, c.x, c.y}, acc);
         }
       if (q < G::N1) {

@@ -142,3 +142,26 @@ def test_trained_warm_start_reduces_iterations(W):
     print(f"iterations to rel. objective 1e-5: zero start {it_cold.mean():.1f}, warm start {it_warm.mean():.1f}")
     assert all(r["converged"] for r in warm) and all(r["converged"] for r in cold)
     assert it_warm.mean() < it_cold.mean()
+
+
+@pytest.mark.parametrize("n,J", [(16, 2), (32, 1), (64, 1)])
+def test_infinite_coefficient_reaches_its_neighbourhood(W, n, J):
+    """With positive weights an infinite coefficient makes exactly the 7 x 7
+    positions (circular) around it infinite, in every channel of its stack, and
+    every other output stays finite: sides 4 to 32, each channel."""
+    net = W.Cnn(n, J, 32, seed=5)
+    p = np.abs(np.random.default_rng(2).standard_normal(net.nparam)).astype(np.float32) * 0.05 + 0.01
+    net.set_params(p)
+    stacks = [(0, 1, n >> J)] + [((n >> l) ** 2, 3, n >> l) for l in range(J, 0, -1)]   # offset, channels, side
+    for off, chans, s in stacks:
+        for c in range(chans):
+            x0 = np.random.default_rng(3).random(n * n).astype(np.float32)
+            r, q = s - 2, 1
+            x0[off + c * s * s + r * s + q] = np.inf
+            out = net.predict(dev(x0)).cpu().numpy()
+            hit = np.zeros((s, s), bool)
+            hit[np.ix_([(r + d) % s for d in range(-3, 4)], [(q + d) % s for d in range(-3, 4)])] = True
+            want = np.zeros(n * n, bool)
+            want[off:off + chans * s * s] = np.tile(hit.ravel(), chans)
+            assert np.array_equal(out == np.inf, want), (s, c)
+            assert np.all(np.isfinite(out[~want])), (s, c)
