@@ -459,20 +459,22 @@ struct Builder {
   bool log = false;
 
   // The weights' table, where it takes no more than a quarter of the memory that
-  // is free beside the kept entries.
+  // is free beside the kept entries (WDB_BUILD_TABLE=0: never; the same sums).
   void tabulate(int64_t nnz_budget) {
     const int64_t N = static_cast<int64_t>(G.n) * G.n, span = 2 * G.R + 1;
+    const char* off = std::getenv("WDB_BUILD_TABLE");
     size_t free = 0, all = 0;
     WDB_HIP(hipMemGetInfo(&free, &all));
     const size_t entry = 2 * sizeof(int32_t) + sizeof(double);
     const size_t kept = (static_cast<size_t>(nnz_budget) + kBoundaryCap) * entry;
-    if (free < kept || static_cast<size_t>(span * span * N) > (free - kept) / 4 / sizeof(double)) return;
+    const size_t bytes = static_cast<size_t>(span * span * N) * sizeof(double);
     T.tiles = (G.n + kReach - 1) / kReach;
-    try {
-      wt.alloc(span * span * N);
+    const bool fits = !(off && *off == '0') && free >= kept && bytes <= (free - kept) / 4 && try_alloc([&] {
+      wt.alloc(span * span * N);   // no memory after all: taken meanwhile (another thread's build)
       reach.alloc(static_cast<size_t>(span) * T.tiles * T.tiles);
-    } catch (...) {   // taken meanwhile (another thread's build)
-      (void)hipGetLastError();
+    });
+    if (log) std::fprintf(stderr, "[wdb] build: weights' table of %zu bytes %s\n", bytes, fits ? "kept" : "left out");
+    if (!fits) {
       wt.reset();
       reach.reset();
       return;

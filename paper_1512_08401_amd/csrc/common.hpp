@@ -87,6 +87,20 @@ struct DevBuf {
   size_t bytes() const { return n * sizeof(T); }
 };
 
+// Runs `alloc`; false where the device has no memory for it.  Any other failure
+// passes on.
+template <typename F>
+bool try_alloc(F&& alloc) {
+  try {
+    alloc();
+    return true;
+  } catch (const Error& e) {
+    if (e.code != WDB_ERR_OOM) throw;
+    (void)hipGetLastError();
+    return false;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Filters (host, float64).
 // ---------------------------------------------------------------------------

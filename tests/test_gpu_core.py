@@ -215,6 +215,25 @@ def test_build_keeps_the_largest_entries_exactly(W, monkeypatch, field, name, J,
         assert th.info()["threshold"] == mag[order[K - 1]], K
 
 
+@pytest.mark.parametrize("rule", ["naive", "scale"])
+@pytest.mark.parametrize("field,name,J", [(synth.psf_rotating(64, 2.5, 1.0), "haar", 3),
+                                          (synth.psf_rotating(32, 2.0, 0.7), "db4", 1),
+                                          (synth.psf_isotropic(64, 0.5, 5.0), "sym6", 2)])
+def test_build_without_the_weights_table_is_the_same(W, monkeypatch, capfd, field, name, J, rule):
+    """Weights evaluated where they are used, as where their table does not fit:
+    the same matrix to the last bit (the same terms in the same order)."""
+    n = field.n
+    monkeypatch.setenv("WDB_LOG", "1")
+    got = []
+    for table in ("1", "0"):
+        monkeypatch.setenv("WDB_BUILD_TABLE", table)
+        th = W.build_theta(field, name, J, 20 * n * n + 3, rule=rule)
+        assert ("bytes kept" in capfd.readouterr().err) == (table == "1")
+        got.append((*th.export(), th.info()["threshold"]))
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("case", ["haar64_iso", "db4_32_aniso", "haar16_cut"])
 def test_convolution_build_matches_alg3_oracle(W, case):
     """A stationary field takes the fast path (one column per subband, circulant
