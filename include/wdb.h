@@ -141,9 +141,9 @@ typedef struct {
  * WDB_BUILD_GENERAL=1 to force the general build.  The result is the same
  * Theta_K up to rounding of the values (and the order of near-equal
  * magnitudes at the cut).
- * The general build keeps a table of all PSF weights (8 (2 R + 1)^2 n^2 bytes,
- * R the PSF radius) while it runs if that is at most a quarter of the device
- * memory free beside the kept entries; without it (or with
+ * The general build keeps a table of the PSF weights (8 (R + 1) (2 R + 1) n^2
+ * bytes, R the PSF radius) while it runs if that is at most an eighth of the
+ * device memory free beside the kept entries; without it (or with
  * WDB_BUILD_TABLE=0) it evaluates them where they are used, with the same
  * result but several times slower.  WDB_LOG=1 prints which.
  * `field` and its arrays are host memory, read during the call.

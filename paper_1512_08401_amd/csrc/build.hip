@@ -132,12 +132,12 @@ __device__ inline void handle(const Select& S, double v, double sb, int a, int b
   }
 }
 
-// Normalised weights of all sources: wt[((dy + R) (2R + 1) + dx + R) N + s].
+// Normalised weights of all sources: wt[(dy (2R + 1) + dx + R) N + s], dy = 0 .. R.
 __global__ __launch_bounds__(256) void k_weights(PsfDev P, double* __restrict__ wt) {
   const int64_t N = static_cast<int64_t>(P.n) * P.n;
   const int64_t s = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (s >= N) return;
-  const int dy = static_cast<int>(blockIdx.y) - P.R;
+  const int dy = static_cast<int>(blockIdx.y);
   for (int dx = -P.R; dx <= P.R; ++dx) {
     const double w = psf_unnormalised(P, s, dy, dx);
     wt[(static_cast<int64_t>(blockIdx.y) * (2 * P.R + 1) + dx + P.R) * N + s] = w != 0.0 ? w / P.Z[s] : 0.0;
@@ -148,14 +148,15 @@ constexpr int kReach = 16;   // side of the tiles whose reach is kept
 
 // Table of the field's weights and, per row offset and kReach x kReach tile
 // (source rows, target columns), the column offsets with a weight other than 0.
+// Row offsets below 0 read the weights and offsets of -dy, -dx.
 struct Weights {
   const double* wt = nullptr;   // nullptr: weights are evaluated where they are used
-  short2* reach = nullptr;      // [dy + R][row tile][column tile]
+  short2* reach = nullptr;      // [dy][row tile][column tile], dy = 0 .. R
   int tiles = 0;
 };
 
 // Reach of the sources of rows 16 blockIdx.y .. and of all columns that a target of
-// columns 16 blockIdx.x .. meets, at dy = blockIdx.z - R.
+// columns 16 blockIdx.x .. meets, at dy = blockIdx.z.
 __global__ __launch_bounds__(256) void k_weight_reach(int n, int R, Weights T) {
   __shared__ int lo, hi;
   if (threadIdx.x == 0) {
@@ -199,13 +200,16 @@ __device__ __forceinline__ double blurred_atom_table(const Weights& T, int n, in
   double acc = 0.0;
   for (int dy = dy0; dy <= dy1; ++dy) {
     const int tr = orow - R - dy, sr = (A.r0 + tr) & (n - 1);
-    const short2 d = T.reach[(static_cast<int64_t>(dy + R) * T.tiles + sr / kReach) * T.tiles + ic / kReach];
-    const int lo = max(dx0, static_cast<int>(d.x)), hi = min(dx1, static_cast<int>(d.y));
+    const int up = dy < 0 ? -dy : dy;
+    const short2 d = T.reach[(static_cast<int64_t>(up) * T.tiles + sr / kReach) * T.tiles + ic / kReach];
+    const int lo = max(dx0, dy < 0 ? -static_cast<int>(d.y) : static_cast<int>(d.x));
+    const int hi = min(dx1, dy < 0 ? -static_cast<int>(d.x) : static_cast<int>(d.y));
+    const int64_t step = dy < 0 ? -N : N;
     const double vr = A.fr[tr];
-    const double* w = T.wt + (static_cast<int64_t>(dy + R) * (2 * R + 1) + R) * N + static_cast<int64_t>(sr) * n;
+    const double* w = T.wt + (static_cast<int64_t>(up) * (2 * R + 1) + R) * N + static_cast<int64_t>(sr) * n;
     // a weight of 0 leaves acc as it is (acc is never -0, the filters are finite)
 #pragma unroll 8
-    for (int dx = lo; dx <= hi; ++dx) acc += (vr * A.fc[ocol - R - dx]) * w[dx * N + ((ic - dx) & (n - 1))];
+    for (int dx = lo; dx <= hi; ++dx) acc += (vr * A.fc[ocol - R - dx]) * w[dx * step + ((ic - dx) & (n - 1))];
   }
   return acc;
 }
@@ -458,20 +462,20 @@ struct Builder {
   hipStream_t s = nullptr;
   bool log = false;
 
-  // The weights' table, where it takes no more than a quarter of the memory that
-  // is free beside the kept entries (WDB_BUILD_TABLE=0: never; the same sums).
+  // The weights' table, where there is room for it beside the kept entries
+  // (WDB_BUILD_TABLE=0: never; the same sums).
   void tabulate(int64_t nnz_budget) {
-    const int64_t N = static_cast<int64_t>(G.n) * G.n, span = 2 * G.R + 1;
+    const int64_t N = static_cast<int64_t>(G.n) * G.n, rows = G.R + 1;
     const char* off = std::getenv("WDB_BUILD_TABLE");
     size_t free = 0, all = 0;
     WDB_HIP(hipMemGetInfo(&free, &all));
     const size_t entry = 2 * sizeof(int32_t) + sizeof(double);
     const size_t kept = (static_cast<size_t>(nnz_budget) + kBoundaryCap) * entry;
-    const size_t bytes = static_cast<size_t>(span * span * N) * sizeof(double);
+    const size_t bytes = weight_table_bytes(G.n, G.R);
     T.tiles = (G.n + kReach - 1) / kReach;
-    const bool fits = !(off && *off == '0') && free >= kept && bytes <= (free - kept) / 4 && try_alloc([&] {
-      wt.alloc(span * span * N);   // no memory after all: taken meanwhile (another thread's build)
-      reach.alloc(static_cast<size_t>(span) * T.tiles * T.tiles);
+    const bool fits = !(off && *off == '0') && bytes <= weight_table_room(free, kept) && try_alloc([&] {
+      wt.alloc(bytes / sizeof(double));   // fails if the memory was taken meanwhile (another thread)
+      reach.alloc(static_cast<size_t>(rows) * T.tiles * T.tiles);
     });
     if (log) std::fprintf(stderr, "[wdb] build: weights' table of %zu bytes %s\n", bytes, fits ? "kept" : "left out");
     if (!fits) {
@@ -481,9 +485,9 @@ struct Builder {
     }
     T.wt = wt.p;
     T.reach = reach.p;
-    hipLaunchKernelGGL(k_weights, dim3(static_cast<unsigned>((N + 255) / 256), static_cast<unsigned>(span)), dim3(256),
+    hipLaunchKernelGGL(k_weights, dim3(static_cast<unsigned>((N + 255) / 256), static_cast<unsigned>(rows)), dim3(256),
                        0, s, psf.dev(), wt.p);
-    hipLaunchKernelGGL(k_weight_reach, dim3(T.tiles, T.tiles, static_cast<unsigned>(span)), dim3(256), 0, s, G.n, G.R,
+    hipLaunchKernelGGL(k_weight_reach, dim3(T.tiles, T.tiles, static_cast<unsigned>(rows)), dim3(256), 0, s, G.n, G.R,
                        T);
     WDB_HIP(hipGetLastError());
   }

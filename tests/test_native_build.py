@@ -27,3 +27,7 @@ def _run(tmp_path, name):
 
 def test_only_missing_memory_leaves_the_table_out(tmp_path):
     _run(tmp_path, "try_alloc_check")
+
+
+def test_weights_table_takes_at_most_an_eighth_of_the_free_memory(tmp_path):
+    _run(tmp_path, "table_room_check")
