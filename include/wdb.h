@@ -468,7 +468,7 @@ wdb_status wdb_dwt(int32_t n, int32_t wavelet, int32_t levels, const float* in, 
  * image): in/out are device arrays of count * n * n floats, image i at i n^2,
  * and must not overlap.  Up to 32 images share a launch.  Results equal
  * wdb_dwt's for each image, bit for bit.  For a forward transform of images of
- * side 2048 and more it allocates 2 n^2 / 4 floats of scratch per image of a
+ * side 2048 and more it allocates about n^2 / 16 floats of scratch per image of a
  * launch; synchronises `stream` before returning.  Errors: as wdb_dwt, and WDB_ERR_ARG for
  * count < 1. */
 wdb_status wdb_dwt_batched(int32_t n, int32_t wavelet, int32_t levels, int32_t count, const float* in,

@@ -392,15 +392,18 @@ LanczosResult lanczos_core(int64_t N, const std::function<void(const double*, do
 // Power iteration on D^-1/2 A^T A D^-1/2 (d = nullptr: identity), float64.
 double power_iteration(wdb_theta* th, const double* start_host, const double* dinv_sqrt,
                        double tol, int max_iters, int* iters_out, hipStream_t s, bool* converged_out = nullptr);
-// Forward/inverse float32 transform on device.  The forward one needs scratch
-// (n*n/4 floats at each of a and b) only where dwt_needs_scratch says so.
-bool dwt_needs_scratch(int n, int levels);
+// Forward/inverse float32 transform on device.  The forward one needs the scratch
+// floats at a and b that dwt_scratch says (at most n*n/4 each, none below a side of
+// 2048).
+struct DwtScratch {
+  size_t a = 0, b = 0;
+};
+DwtScratch dwt_scratch(int n, int levels);
 void dwt_forward(int n, int levels, const Filter& f, const float* in, float* out,
                  float* scratch_a, float* scratch_b, hipStream_t s);
 void dwt_inverse(int n, int levels, const Filter& f, const float* in, float* out, hipStream_t s);
 // The same for `count` images, up to 32 per launch; scratch_a[i], scratch_b[i]:
-// n*n/4 floats each for image i where scratch is needed, and images in one
-// group of 32 must not share scratch.
+// image i's scratch, which images in one group of 32 must not share.
 void dwt_forward_many(int n, int levels, const Filter& f, int count, const float* const* in, float* const* out,
                       float* const* scratch_a, float* const* scratch_b, hipStream_t s);
 void dwt_inverse_many(int n, int levels, const Filter& f, int count, const float* const* in, float* const* out,

@@ -440,15 +440,20 @@ int launch_levels(int M, int left) {
 
 }  // namespace
 
-bool dwt_needs_scratch(int n, int levels) {
-  int M = n, left = levels;
+DwtScratch dwt_scratch(int n, int levels) {
+  DwtScratch need;
+  int M = n, left = levels, turn = 0;
   while (M > kTailSide && left > 0) {
     const int nl = launch_levels(M, left);
     M >>= nl;
     left -= nl;
-    if (left > 0 && M > kTailSide) return true;
+    if (left > 0 && M > kTailSide) {   // the approximation another launch of many blocks reads
+      size_t& part = turn ? need.b : need.a;
+      part = std::max(part, static_cast<size_t>(M) * M);
+      turn ^= 1;
+    }
   }
-  return false;
+  return need;
 }
 
 void dwt_forward_many(int n, int levels, const Filter& f, int count, const float* const* in, float* const* out,
@@ -579,12 +584,12 @@ extern "C" wdb_status wdb_dwt(int32_t n, int32_t wavelet, int32_t levels, const 
   wdb::Filter f = wdb::make_filter(wavelet);
   wdb::check_geometry(n, levels, static_cast<int>(f.h.size()));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const size_t q = static_cast<size_t>(n / 2) * (n / 2);
-  wdb::DevBuf<float> scratch(!inverse && wdb::dwt_needs_scratch(n, levels) ? 2 * q : 0);
+  const wdb::DwtScratch need = inverse ? wdb::DwtScratch{} : wdb::dwt_scratch(n, levels);
+  wdb::DevBuf<float> scratch(need.a + need.b);
   if (inverse)
     wdb::dwt_inverse(n, levels, f, in, out, s);
   else
-    wdb::dwt_forward(n, levels, f, in, out, scratch.p, scratch.p + q, s);
+    wdb::dwt_forward(n, levels, f, in, out, scratch.p, scratch.p + need.a, s);
   WDB_HIP(hipStreamSynchronize(s));
   WDB_API_END
 }
@@ -603,16 +608,16 @@ extern "C" wdb_status wdb_dwt_batched(int32_t n, int32_t wavelet, int32_t levels
   const char* oe = reinterpret_cast<const char*>(out + N * count);
   WDB_REQUIRE(ie <= ob || oe <= ib, WDB_ERR_ARG, "in and out must not overlap");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const size_t q = static_cast<size_t>(n / 2) * (n / 2);
+  const wdb::DwtScratch need = inverse ? wdb::DwtScratch{} : wdb::dwt_scratch(n, levels);
   const int nsc = std::min(count, wdb::kBatch);
-  wdb::DevBuf<float> scratch(!inverse && wdb::dwt_needs_scratch(n, levels) ? 2 * q * nsc : 0);
+  wdb::DevBuf<float> scratch((need.a + need.b) * nsc);
   std::vector<const float*> ip(count);
   std::vector<float*> op(count), sa(count), sb(count);
   for (int i = 0; i < count; ++i) {
     ip[i] = in + N * i;
     op[i] = out + N * i;
-    sa[i] = scratch.p + 2 * q * (i % nsc);   // images of one launch use distinct scratch; launches are in order
-    sb[i] = sa[i] + q;
+    sa[i] = scratch.p + (need.a + need.b) * (i % nsc);   // images of one launch use distinct scratch; launches are in order
+    sb[i] = sa[i] + need.a;
   }
   if (inverse)
     wdb::dwt_inverse_many(n, levels, f, count, ip.data(), op.data(), s);
