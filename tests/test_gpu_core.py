@@ -120,6 +120,22 @@ def test_inverse_dwt_of_many_levels_matches_oracle(W, name, n, J, count):
         assert np.max(np.abs(v[i] - vo)) <= 2e-6 * np.max(np.abs(vo))
 
 
+@pytest.mark.parametrize("name", ["haar", "db4", "sym6"])
+def test_dwt_of_one_level_at_side_128(W, name):
+    """A single level of side 128 goes to blocks of 16 x 16 positions, more levels to
+    one block per image: both against the oracle (bar of the tests above), with
+    the first level's details equal bit for bit, and a batch like one image."""
+    n = 128
+    u = np.random.default_rng(4).random((35, n, n)).astype(np.float32)
+    one = host(W.dwt_batched(dev(u.reshape(35, -1)), name, 1)).reshape(35, -1)
+    two = host(W.dwt_batched(dev(u.reshape(35, -1)), name, 2)).reshape(35, -1)
+    assert np.array_equal(one[:, n * n // 4:], two[:, n * n // 4:])
+    for i in (0, 34):
+        xo = dwt.dwt2(u[i].astype(np.float64), filters.by_name(name), 1)
+        assert np.max(np.abs(one[i] - xo)) <= 2e-6 * np.max(np.abs(xo))
+        assert np.array_equal(one[i], host(W.dwt(dev(u[i]).reshape(-1), name, 1)))
+
+
 def test_dwt_many_images_match_single(W):
     """More images than a launch takes, and enough blocks for the larger tile."""
     n, J, count = 64, 2, 261
