@@ -191,7 +191,7 @@ template <int L>
 __global__ __launch_bounds__(kTailThreads) void k_dwt_fwd_tail(FwdPtrs P, int lm, int levels, Taps t) {
   extern __shared__ __align__(16) float lds[];
   int M = 1 << lm;
-  const float* __restrict__ A = P.src[blockIdx.z];
+  const float* A = P.src[blockIdx.z];   // may be out: all of it is read before the first store
   float* out = P.out[blockIdx.z];
   float* X = lds;
   float2* R = reinterpret_cast<float2*>(lds + M * M);
