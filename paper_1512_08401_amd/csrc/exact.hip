@@ -85,40 +85,6 @@ __global__ __launch_bounds__(256) void k_exact_coef(PsfDev P, double* __restrict
   }
 }
 
-// Reach of a tile of sources (blockIdx.x), thread = source.
-__global__ __launch_bounds__(kT * kT) void k_exact_reach(PsfDev P, int ntile, short2* __restrict__ reach) {
-  __shared__ int lo, hi;
-  const int r = static_cast<int>(blockIdx.x) / ntile * kT + static_cast<int>(threadIdx.x) / kT;
-  const int c = static_cast<int>(blockIdx.x) % ntile * kT + static_cast<int>(threadIdx.x) % kT;
-  const bool on = r < P.n && c < P.n;
-  const int64_t s = on ? static_cast<int64_t>(r) * P.n + c : 0;
-  const double a = P.sM[s], b = P.sm[s], cs = P.c[s], sn = P.s[s];
-  // the ellipse's bounding box and one more pixel; the formula decides
-  const int hx = min(static_cast<int>(floor(P.trunc * sqrt(a * a * cs * cs + b * b * sn * sn))) + 1, P.R);
-  const int hy = min(static_cast<int>(floor(P.trunc * sqrt(a * a * sn * sn + b * b * cs * cs))) + 1, P.R);
-  for (int dy = -P.R; dy <= P.R; ++dy) {
-    if (threadIdx.x == 0) {
-      lo = P.R + 1;
-      hi = -P.R - 1;
-    }
-    __syncthreads();
-    if (on && dy >= -hy && dy <= hy) {
-      int first = -hx, last = hx;
-      while (first <= hx && psf_q(P, s, dy, first) > P.T2) ++first;
-      while (last >= first && psf_q(P, s, dy, last) > P.T2) --last;
-      if (first <= last) {
-        atomicMin(&lo, first);
-        atomicMax(&hi, last);
-      }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0)
-      reach[static_cast<int64_t>(blockIdx.x) * (2 * P.R + 1) + dy + P.R] = make_short2(static_cast<short>(lo),
-                                                                                      static_cast<short>(hi));
-    __syncthreads();
-  }
-}
-
 // a b + c with c from scalar registers.  (The compiler would copy each constant
 // into the accumulator of a two-address v_fmac: a third more instructions here.)
 __device__ __forceinline__ double fma_const(double a, double b, double c) {
@@ -143,18 +109,73 @@ __device__ __forceinline__ double exp2_neg(double x) {
   return ldexp(fma(p, r, 1.0), __double2loint(t));
 }
 
+// Scaled q of coefficients k at offset (dy, dx).
+__device__ __forceinline__ double scaled_q(double k0, double k1, double k2, double k3, double fy, double fx) {
+  const double u1 = fma(fx, k0, fy * k1), u2 = fma(-fx, k3, fy * k2);
+  return fma(u1, u1, u2 * u2);
+}
+
 // acc + w v, with w the weight (before 1 / Z) of source s, coefficients k, at
 // offset (dy, dx); acc past the cut-off.
 __device__ __forceinline__ double weigh(const ExDev& E, int64_t s, double k0, double k1, double k2, double k3,
                                         int dy, int dx, double fy, double fx, double v, double acc) {
-  const double u1 = fma(fx, k0, fy * k1), u2 = fma(-fx, k3, fy * k2);
-  const double q = fma(u1, u1, u2 * u2);
+  const double q = scaled_q(k0, k1, k2, k3, fy, fx);
   const bool maybe = q <= E.never;
   if (!__any(maybe)) return acc;
   bool in = q <= E.sure;
   if (maybe && !in) in = psf_q(E.P, s, dy, dx) <= E.P.T2;
   const double sum = fma(exp2_neg(q), v, acc);
   return in ? sum : acc;
+}
+
+// Reach at dy = blockIdx.y and at -dy of a tile of sources (blockIdx.x), thread =
+// source.  An interval's ends come from the roots of q in dx, one offset more on
+// either side, and are then tried; what rounding could let in is let in (the
+// products decide).  A block per dy: with all of a tile's in one block and every
+// offset tried with the field's formula, creating the handle took 1.44 ms for 64 x
+// 64 at radius 30 and 6.15 ms for 512 x 512 at radius 27; now 0.79 and 5.4 ms.
+__global__ __launch_bounds__(kT * kT) void k_exact_reach(ExDev E, short2* __restrict__ reach) {
+  __shared__ int lo, hi;
+  const int n = E.P.n, R = E.P.R, dy = blockIdx.y;
+  const int64_t N = static_cast<int64_t>(n) * n;
+  const int r = static_cast<int>(blockIdx.x) / E.ntile * kT + static_cast<int>(threadIdx.x) / kT;
+  const int c = static_cast<int>(blockIdx.x) % E.ntile * kT + static_cast<int>(threadIdx.x) % kT;
+  if (threadIdx.x == 0) {
+    lo = R + 1;
+    hi = -R - 1;
+  }
+  __syncthreads();
+  int first = R + 1, last = -R - 1;
+  if (r < n && c < n) {
+    const int64_t s = static_cast<int64_t>(r) * n + c;
+    const double k0 = E.coef[s], k1 = E.coef[N + s], k2 = E.coef[2 * N + s], k3 = E.coef[3 * N + s];
+    const double fy = static_cast<double>(dy), R1 = static_cast<double>(R);
+    const double a = fma(k0, k0, k3 * k3), mid = -fy * (k0 * k1 - k3 * k2) / a;
+    const double half = sqrt(fmax((E.never - fy * fy * fma(k1, k1, k2 * k2)) / a + mid * mid, 0.0)) + 1.0;
+    // a not-a-number (squares that overflow, PSFs without weights): every offset is tried
+    const bool known = mid - half <= mid + half && a < 1e300;
+    int x0 = known ? static_cast<int>(fmax(floor(mid - half), -R1)) : -R;
+    int x1 = known ? static_cast<int>(fmin(ceil(mid + half), R1)) : R;
+    while (x0 <= x1 && !(scaled_q(k0, k1, k2, k3, fy, static_cast<double>(x0)) <= E.never)) ++x0;
+    while (x1 >= x0 && !(scaled_q(k0, k1, k2, k3, fy, static_cast<double>(x1)) <= E.never)) --x1;
+    if (x0 <= x1) {
+      first = x0;
+      last = x1;
+    }
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    first = min(first, __shfl_xor(first, off));
+    last = max(last, __shfl_xor(last, off));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    atomicMin(&lo, first);
+    atomicMax(&hi, last);
+  }
+  __syncthreads();
+  if (threadIdx.x) return;
+  short2* at = reach + static_cast<int64_t>(blockIdx.x) * (2 * R + 1) + R;
+  at[-dy] = make_short2(static_cast<short>(-hi), static_cast<short>(-lo));   // a PSF is even
+  at[dy] = make_short2(static_cast<short>(lo), static_cast<short>(hi));
 }
 
 // Interval of dx that any source of the tiles covering rows [r0, r1] and columns
@@ -516,11 +537,12 @@ wdb_status wdb_exact_create(const wdb_psf_field* field, int32_t wavelet, int32_t
     const size_t tiles = static_cast<size_t>(ex->ntile) * ex->ntile;
     ex->reach.alloc(tiles * (2 * static_cast<size_t>(ex->F.R) + 1));
     hipLaunchKernelGGL(wdb::k_exact_coef, wdb::pix_grid(N), dim3(256), 0, s, ex->F.dev(), ex->coef.p);
-    hipLaunchKernelGGL(wdb::k_exact_reach, dim3(static_cast<unsigned>(tiles)), dim3(wdb::kT * wdb::kT), 0, s,
-                       ex->F.dev(), ex->ntile, ex->reach.p);
+    hipLaunchKernelGGL(wdb::k_exact_reach, dim3(static_cast<unsigned>(tiles), static_cast<unsigned>(ex->F.R + 1)),
+                       dim3(wdb::kT * wdb::kT), 0, s, wdb::view(ex), ex->reach.p);
     for (auto* b : {&ex->u0, &ex->y, &ex->img, &ex->r, &ex->gimg, &ex->g}) b->alloc(N);
-    ex->sa.alloc(N / 4 + 1);
-    ex->sb.alloc(N / 4 + 1);
+    const wdb::DwtScratch need = wdb::dwt_scratch(ex->n, levels);
+    ex->sa.alloc(need.a);
+    ex->sb.alloc(need.b);
     const int64_t nb = wdb::pix_grid(N).x;
     ex->part.alloc(4 * nb);
     ex->scal.alloc(4);

@@ -175,3 +175,23 @@ def test_exact_sources_without_weights_spread_nothing(W):
     assert np.max(np.abs(v - np.where(none, 0.0, Hv))) <= 1e-7 * np.max(np.abs(Hv))
     u[none] = np.inf
     assert np.max(np.abs(host(ex.apply(dev(u))) - Hu)) <= 1e-7 * np.max(np.abs(Hu))
+
+
+@pytest.mark.parametrize("n,low,high,trunc", [(32, 1e-3, 5.0, 3.0), (64, 0.3, 10.0, 3.0), (16, 1e-9, 2.0, 3.0),
+                                              (32, 5.0, 40.0, 0.3), (64, 0.05, 0.75, 40.0)])
+def test_exact_fields_that_change_from_pixel_to_pixel(W, n, low, high, trunc):
+    """Every source with its own axes (ratios up to 2e9) and angle, some at multiples
+    of pi / 4 where offsets lie on the axes: no offset of a tile's interval is
+    missed.  Bar of the tests above."""
+    rng = np.random.default_rng(n)
+    draw = lambda: np.exp(rng.uniform(np.log(low), np.log(high), n * n))
+    angle = np.where(rng.random(n * n) < 0.3, rng.integers(0, 8, n * n) * (np.pi / 4), rng.uniform(0, 7, n * n))
+    major, minor = draw(), draw()
+    major[0] = high
+    field = types.SimpleNamespace(n=n, sig_major=major, sig_minor=minor, angle=angle, trunc=trunc)
+    print(f"exact n={n} sigma {low}..{high} trunc={trunc}", flush=True)
+    u = rng.standard_normal(n * n).astype(np.float32)
+    Hu, Hv = direct_products(field, u, u)
+    ex = W.Exact(field, "haar", 1)
+    assert np.max(np.abs(host(ex.apply(dev(u))) - Hu)) <= 1e-7 * np.max(np.abs(Hu))
+    assert np.max(np.abs(host(ex.apply(dev(u), adjoint=True)) - Hv)) <= 1e-7 * np.max(np.abs(Hv))
