@@ -21,7 +21,7 @@
 // W right-hand-side values (neighbouring lanes of a tile row read neighbouring
 // columns) and the tile value once for all of them.  Their float64 checks run
 // on the tiles too.  The gathers are bound by the L1's lines: their eight slots
-// lie in two planes [N][4] (up to kDeepMax coefficients), so that each 16-byte load of a tile row is whole
+// lie in two planes [N][4] (see kDeepMax), so that each 16-byte load of a tile row is whole
 // lines, where [N][8] gives every load half of twice as many (24 problems of 256 x
 // 256, per iteration: 150 -> 129 us; with a group's operands under way while the one
 // before it is summed 129 -> 89 us, with the packs' order 89 -> 72 us).  What is
@@ -47,13 +47,21 @@ constexpr int kBlock = 128;   // 2 wavefronts per tile: 4% faster than 4 and 13%
 constexpr int kWave = 64;
 constexpr int kWaves = kBlock / kWave;
 constexpr int kR = 8;                  // right-hand sides per chunk
-// Largest problem of a batch that runs the kernels with operands a group ahead and,
-// on the tiles, slots in planes (DEEP).  Up to here an XCD's stripe of a vector is at
-// most a quarter of its L2 and the tiles' chains bound the launch; beyond, wavefronts
-// in flight count for more than the registers' worth of loads, and a run of columns
-// that begins within a line takes 4 lines in planes and 3 side by side (8 problems
-// of 1024 x 1024 per iteration: dense tiles 279 -> 242 us, kept 294 -> 239 us, sliced
-// ELL 329 -> 296 us; of 512 x 512, with the loads ahead: 85 -> 64, 117 -> 72, 128 -> 98).
+// Coefficients of an operator's packs together up to which its batch runs the kernels
+// with operands a group ahead and, on the tiles, slots in planes (DEEP): below twice
+// this on the tiles, up to three times this on sliced ELL, whose vectors stay side by side.
+// Up to here the XCDs' L2 hold the stripes of the vectors that the packs gather from and
+// the tiles' chains bound the launch; beyond, wavefronts in flight count for more than
+// the registers' worth of loads, and a run of columns that begins within a line takes 4
+// lines in planes and 3 side by side.  us per iteration without -> with, 25 non-zeros a
+// row, for dense tiles / kept values / sliced ELL:
+//   packs of 512 x 512:   1   64 ->  56    69 ->  58   103 ->  82
+//                         2   88 -> 102    96 -> 108   131 -> 117
+//                         3  106 -> 134   122 -> 140   150 -> 146
+//                         4  172 -> 237   183 -> 218   233 -> 271
+//   packs of 256 x 256:   5   74 ->  71    86 ->  74   115 ->  94
+//                         8  100 -> 110   109 -> 118   130 -> 121
+//   one of 1024 x 1024:   1  242 -> 279   239 -> 294   296 -> 329
 constexpr int64_t kDeepMax = 512 * 512;
 
 struct ChunkDev {
@@ -74,7 +82,7 @@ struct ChunkDev {
   float* Cr;         // [N][8] right-hand side of the displacement iteration, x0 - Theta_K anchor
   double* Anc;       // [N][8] float64 anchor
   float* Rr;         // [N][8] residual
-  int g0, gn;        // first chunk of the operator, and their number
+  int g0, gn;        // first of the operator's chunks that take turns with this one, and their number
   int W;             // slots in use (8, 4, 2 or 1): the vectors are [N][W], problem slots [0, W)
   int shift;         // of W = 8: row r's slots 0 .. 3 begin at r << shift and 4 .. 7 half behind
   int64_t half;      // ([N][8]: 3 and 4; two planes [N][4], on the tiles: 2 and 4 N)
@@ -883,8 +891,12 @@ extern "C" wdb_status wdb_solve_batched(int32_t nprob, const wdb_problem* probs,
     }
   }
   const int nch = static_cast<int>(chunks.size());
+  const auto packs_of = [&](wdb_theta* th) { return static_cast<int>((members[th].size() + kR - 1) / kR); };
   bool deep = true;
-  for (const Host& h : chunks) deep &= h.th->N <= kDeepMax;
+  for (wdb_theta* th : order) {
+    const int64_t all = th->N * packs_of(th);
+    deep &= kernel_group(th) == kTiled ? all < 2 * kDeepMax : all <= 3 * kDeepMax;
+  }
   DevBuf<float> pX(tot8), pY(tot8), pX0(tot8), pRr(tot8), pCr(tot8);
   DevBuf<double> pR64(tot8), pAnc(tot8);
   DevBuf<int> pAct(static_cast<size_t>(nch) * (kR + 1));
@@ -931,7 +943,15 @@ extern "C" wdb_status wdb_solve_batched(int32_t nprob, const wdb_problem* probs,
     d.W = h.W;
     d.g0 = c;
     while (d.g0 > 0 && chunks[d.g0 - 1].th == th) --d.g0;
-    d.gn = static_cast<int>((members[th].size() + kR - 1) / kR);
+    d.gn = packs_of(th);
+    // of a large operator's two packs the second takes no turns with the first if it
+    // has one or two problems: its blocks end long before the full pack's, and between
+    // those they cost more than the entries read again (9 of 512 x 512, us per
+    // iteration: dense tiles 88 -> 81, kept values 106 -> 84, sliced ELL 108 -> 100)
+    if (d.gn == 2 && N >= kDeepMax && chunks[d.g0 + 1].W <= 2) {
+      d.g0 = c;
+      d.gn = 1;
+    }
     d.pinv = pre ? th->pinv : nullptr;
     d.tau = static_cast<float>(tau);
     d.act = pAct.p + static_cast<int64_t>(c) * (kR + 1);

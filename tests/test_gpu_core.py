@@ -1125,6 +1125,30 @@ def test_batched_packs_equal_packs_of_one(W, layout):
 
 
 @pytest.mark.parametrize("layout", ["sell", "dense", "kept"])
+@pytest.mark.parametrize("n,count,checked", [(64, 17, (0, 9, 15, 16)), (64, 26, (3, 23, 24, 25)),
+                                             (256, 59, (0, 8, 55, 58)), (512, 9, (7, 8)), (512, 26, (3, 24, 25))])
+def test_batched_packs_of_every_arrangement_keep_the_iterates(W, layout, n, count, checked):
+    """Packs of an operator that take turns, the last of them of one, two or four
+    slots, and (9 problems of 512 x 512) a second pack by itself, with loads ahead and
+    planes and (59 of 256 x 256 and more on the tiles) without: a problem's
+    iterate is that of a batch of its own, to the last bit, and it stops at the same check."""
+    th = W.build_theta(synth.psf_rotating(n, 2.5, 1.0), "haar", 3, 12 * n * n + 5)
+    th.lipschitz_lanczos()
+    if layout == "sell":
+        th.set_kernel_layout(16, 0)
+    else:
+        th.set_kernel_layout(8, 3)
+        th.set_tile_values(layout == "kept")
+    g = torch.Generator("cuda").manual_seed(n + count)
+    probs = [(th, torch.rand(th.N, device="cuda", generator=g), 1e-3 * (1 + i % 5)) for i in range(count)]
+    xs, infos = W.solve_batched(probs, 30, check_every=10, tol=0.05)
+    for i in checked:
+        x1, info1 = W.solve_batched([probs[i]], 30, check_every=10, tol=0.05)
+        assert torch.equal(xs[i], x1[0]), i
+        assert infos[i]["iters"] == info1[0]["iters"], i
+
+
+@pytest.mark.parametrize("layout", ["sell", "dense", "kept"])
 def test_batched_with_a_large_operator_keeps_the_iterates(W, layout):
     """A batch that holds a problem of more than 512 x 512 coefficients runs the
     kernels without loads ahead and planes: the small problems' iterates stay
