@@ -86,6 +86,38 @@ def test_network_tiles_match_oracle(W, n, J, B):
     assert again == loss and np.array_equal(g, g2)   # every sum has a fixed order
 
 
+@pytest.mark.parametrize("n,J,B", [(32, 1, 301), (64, 3, 101), (128, 2, 21)])
+def test_blocks_of_many_tiles_match_oracle(W, n, J, B):
+    """More tiles than compute units (504 to 707 on 256), so blocks walk several
+    tiles, unequally many: 16 x 16 tiles, tiles that cover a side of 8 and 8 x
+    32 tiles.  Bars of the test above."""
+    net = W.Cnn(n, J, 32, seed=5)
+    rng = np.random.default_rng(n + J)
+    p = (rng.standard_normal(net.nparam) * 0.05).astype(np.float32)
+    net.set_params(p)
+    pr = net.get_params(rounded=True).astype(np.float64)
+    x0 = rng.standard_normal((B, n * n)).astype(np.float32)
+    tgt = rng.standard_normal((B, n * n)).astype(np.float32)
+    print(f"network n={n} J={J} B={B}", flush=True)
+    pred = net.predict(dev(x0).reshape(-1)).cpu().numpy().reshape(B, -1)
+    pred_o = ocnn.forward(pr, x0.astype(np.float64), n, J, 32)
+    assert np.max(np.abs(pred - pred_o)) <= 1e-5 * np.max(np.abs(pred_o))
+    for i in (0, B // 2, B - 1):   # an image's tiles do not depend on the blocks they fall to
+        assert np.array_equal(pred[i], net.predict(dev(x0[i])).cpu().numpy())
+    loss, g = net.loss_grad(dev(x0).reshape(-1), dev(tgt).reshape(-1))
+    loss_o, g_o = ocnn.loss_and_grad(pr, x0.astype(np.float64), tgt.astype(np.float64), n, J, 32)
+    assert abs(loss - loss_o) <= 1e-6 * loss_o
+    scale, pos = np.max(np.abs(g_o)), 0
+    for shp in ocnn.param_shapes(n, J, 32):
+        k = int(np.prod(shp))
+        assert np.max(np.abs(g[pos:pos + k] - g_o[pos:pos + k])) <= 1e-4 * scale
+        assert np.linalg.norm(g[pos:pos + k] - g_o[pos:pos + k]) <= 1e-4 * max(np.linalg.norm(g_o[pos:pos + k]),
+                                                                              1e-3 * scale)
+        pos += k
+    again, g2 = net.loss_grad(dev(x0).reshape(-1), dev(tgt).reshape(-1))
+    assert again == loss and np.array_equal(g, g2)
+
+
 def test_adam_step_matches_closed_form(W):
     n, J, F = 32, 2, 32
     net = W.Cnn(n, J, F, seed=6)
