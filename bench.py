@@ -692,18 +692,21 @@ def run_conv(args):
 
 def cnn_flops(n, levels, F=32):
     """Algorithmic FLOPs per image of the warm-start network: (inference,
-    training step).  Per position of a stack with C channels the three
-    convolutions cost 2*9*C*F, 2*9*F*F and 2*9*F*C; a training step runs the
-    forward pass, the stack's recomputed first two convolutions, both
-    gradients of the last two and the weight gradient of the first."""
+    training step, the training step's bf16 FLOPs).  Per position of a stack with
+    C channels the three convolutions cost 2*9*C*F, 2*9*F*F and 2*9*F*C; a
+    training step runs the forward pass, both gradients of the last two and the
+    weight gradient of the first.  On the matrix cores a float32 operand is three
+    exact bf16 parts: three products where the other operand is a bf16 weight, six
+    in the weight gradients."""
     sides = [n >> levels] + [n >> l for l in range(levels, 0, -1)]
     chans = [1] + [3] * levels
-    inf = train = 0
+    inf = train = bf16 = 0
     for s, C in zip(sides, chans):
         c1, c2, c3 = 18 * C * F, 18 * F * F, 18 * F * C
         inf += s * s * (c1 + c2 + c3)
-        train += s * s * (3 * c1 + 4 * c2 + 3 * c3)
-    return inf, train
+        train += s * s * (2 * c1 + 3 * c2 + 3 * c3)
+        bf16 += s * s * (3 * (c1 + 2 * c2 + 2 * c3) + 6 * (c1 + c2 + c3))
+    return inf, train, bf16
 
 
 def run_cnn(args):
@@ -711,8 +714,9 @@ def run_cnn(args):
     shapes (256x256 coefficients, 4 levels, 32 channels) with a batch of 32:
     K timed Adam training steps, then K timed inference passes, inputs resident
     in HBM.  Roofline: the convolutions' algorithmic FLOPs per step over the
-    step time, against a third of the dense bf16 matrix-core peak (float32
-    operands are split into exact bf16 parts, three products each)."""
+    step time, against the rate at which the dense bf16 matrix-core peak runs the
+    bf16 products they take (three each in the forward pass and the data
+    gradients, six in the weight gradients)."""
     import torch
     import synth
     from paper_1512_08401_amd import wdb
@@ -739,7 +743,8 @@ def run_cnn(args):
     torch.cuda.synchronize()
     t_train = e0.elapsed_time(e1) / 1e3 / args.steps
     t_inf = e1.elapsed_time(e2) / 1e3 / args.steps
-    f_inf, f_train = cnn_flops(n, J)
+    f_inf, f_train, f_bf16 = cnn_flops(n, J)
+    peak = 2500.0 * f_train / f_bf16
     ach = B * f_train / t_train / 1e12
     log(f"train step {t_train * 1e3:.3f} ms, inference {t_inf * 1e3:.3f} ms (batch {B})")
     return {"metric": "warm-start network training steps/s", "value": round(1.0 / t_train, 2), "unit": "steps/s",
@@ -747,8 +752,8 @@ def run_cnn(args):
             "ms_per_step": round(t_train * 1e3, 4), "dtype": "bf16 weights, f32 compute", "data": "synthetic",
             "config": {"workload": f"cnn256: {n}x{n} coefficients, {J} levels, 32 channels, batch {B}"},
             "inference_ms": round(t_inf * 1e3, 4), "images_per_s_inference": round(B / t_inf, 1),
-            "roofline": {"bound": "mfma", "achieved": round(ach, 3), "peak": round(2500.0 / 3, 1), "unit": "TFLOP/s",
-                         "frac": round(ach / (2500.0 / 3), 4), "traffic": None,
+            "roofline": {"bound": "mfma", "achieved": round(ach, 3), "peak": round(peak, 1), "unit": "TFLOP/s",
+                         "frac": round(ach / peak, 4), "traffic": None,
                          "kernel": "whole training step (convolution FLOPs / step time)",
                          "flops_per_step": B * f_train},
             "inference_tflops": round(B * f_inf / t_inf / 1e12, 3)}

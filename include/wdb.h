@@ -498,7 +498,8 @@ wdb_status wdb_blur(const wdb_psf_field* field, const float* u, float* out, void
  * so this is the problem before thresholding (Theta = Psi^* H Psi, all of
  * it).  H and H^* evaluate the truncated PSFs of the field on the fly in
  * float64 (the formula and cut-off of wdb_blur), accumulating in float64;
- * images and coefficients are float32.  Device memory: about 110 N bytes.
+ * images and coefficients are float32.  Device memory: about
+ * 105 + (2 R + 1) / 64 bytes per pixel, R the PSF radius.
  * ------------------------------------------------------------------------- */
 typedef struct wdb_exact wdb_exact;
 

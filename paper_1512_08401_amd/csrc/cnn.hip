@@ -889,7 +889,10 @@ __device__ __forceinline__ void bwd_stack(const StackArg& S, const float* __rest
 // (per 8 x 32 tile 40 thousand cycles, 13 of them products, two thirds of these
 // dW2).  The nine taps' accumulators are split over two wavefronts, so that two
 // fit on a SIMD and one's loads and splits run beside the other's products
-// (with one wavefront per SIMD holding them all: 316 us, this one 290 us).  A
+// (with one wavefront per SIMD holding them all: 316 us, this one 290 us).  They
+// fit with 256 registers each because the compiler keeps 324 values in scratch
+// (700 bytes a lane, over the three forms of bwd_stack together); what these cost
+// is not known apart from the rest.  A
 // training step of 32 images of 256 x 256 takes 0.42 ms (forward 0.12 ms, this
 // kernel 0.29 ms); with float32 matrix products, a kernel per layer and the
 // forward pass twice it took 1.29 ms.
