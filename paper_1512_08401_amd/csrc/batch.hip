@@ -47,14 +47,15 @@ constexpr int kBlock = 128;   // 2 wavefronts per tile: 4% faster than 4 and 13%
 constexpr int kWave = 64;
 constexpr int kWaves = kBlock / kWave;
 constexpr int kR = 8;                  // right-hand sides per chunk
-// Coefficients of an operator's packs together up to which its batch runs the kernels
-// with operands a group ahead and, on the tiles, slots in planes (DEEP): below twice
-// this on the tiles, up to three times this on sliced ELL, whose vectors stay side by side.
-// Up to here the XCDs' L2 hold the stripes of the vectors that the packs gather from and
-// the tiles' chains bound the launch; beyond, wavefronts in flight count for more than
-// the registers' worth of loads, and a run of columns that begins within a line takes 4
-// lines in planes and 3 side by side.  us per iteration without -> with, 25 non-zeros a
-// row, for dense tiles / kept values / sliced ELL:
+// An operator's packs together hold at most twice (on the tiles) or three times (on
+// sliced ELL, whose vectors stay side by side) this many coefficients in a batch that
+// runs the kernels with operands a group ahead and, on the tiles, slots in planes
+// (DEEP).  Up to there the XCDs' L2 hold the stripes of the vectors that the packs
+// gather from and the tiles' chains bound the launch; beyond, wavefronts in flight
+// count for more than the registers' worth of loads, and a run of columns that begins
+// within a line takes 4 lines in planes and 3 side by side.  us per iteration without
+// -> with, for dense tiles / kept values / sliced ELL (25 non-zeros a row, a rotating
+// PSF; with an isotropic one 2 packs of 512 x 512 take 126 -> 126, 132 -> 132, 195 -> 161):
 //   packs of 512 x 512:   1   64 ->  56    69 ->  58   103 ->  82
 //                         2   88 -> 102    96 -> 108   131 -> 117
 //                         3  106 -> 134   122 -> 140   150 -> 146
@@ -62,6 +63,9 @@ constexpr int kR = 8;                  // right-hand sides per chunk
 //   packs of 256 x 256:   5   74 ->  71    86 ->  74   115 ->  94
 //                         8  100 -> 110   109 -> 118   130 -> 121
 //   one of 1024 x 1024:   1  242 -> 279   239 -> 294   296 -> 329
+// Two packs of 512 x 512 are within the bound for the sake of smaller operators beside
+// them (19 of 256 x 256 on sliced ELL and 13 of 512 x 512 on dense tiles, 120 iterations:
+// 25.3 -> 24.4 ms).
 constexpr int64_t kDeepMax = 512 * 512;
 
 struct ChunkDev {
@@ -895,7 +899,7 @@ extern "C" wdb_status wdb_solve_batched(int32_t nprob, const wdb_problem* probs,
   bool deep = true;
   for (wdb_theta* th : order) {
     const int64_t all = th->N * packs_of(th);
-    deep &= kernel_group(th) == kTiled ? all < 2 * kDeepMax : all <= 3 * kDeepMax;
+    deep &= all <= (kernel_group(th) == kTiled ? 2 : 3) * kDeepMax;
   }
   DevBuf<float> pX(tot8), pY(tot8), pX0(tot8), pRr(tot8), pCr(tot8);
   DevBuf<double> pR64(tot8), pAnc(tot8);
@@ -945,10 +949,11 @@ extern "C" wdb_status wdb_solve_batched(int32_t nprob, const wdb_problem* probs,
     while (d.g0 > 0 && chunks[d.g0 - 1].th == th) --d.g0;
     d.gn = packs_of(th);
     // of a large operator's two packs the second takes no turns with the first if it
-    // has one or two problems: its blocks end long before the full pack's, and between
-    // those they cost more than the entries read again (9 of 512 x 512, us per
-    // iteration: dense tiles 88 -> 81, kept values 106 -> 84, sliced ELL 108 -> 100)
-    if (d.gn == 2 && N >= kDeepMax && chunks[d.g0 + 1].W <= 2) {
+    // has few slots: its blocks end long before the full pack's, and between those they
+    // cost more than the entries read again (512 x 512, us per iteration, 9 problems:
+    // dense tiles 93 -> 87, kept values 101 -> 90, sliced ELL 108 -> 103; 12 problems: 96 ->
+    // 79, 101 -> 99, and on sliced ELL, which therefore keeps its turns, 107 -> 121)
+    if (d.gn == 2 && N >= kDeepMax && chunks[d.g0 + 1].W <= (kernel_group(th) == kTiled ? 4 : 2)) {
       d.g0 = c;
       d.gn = 1;
     }

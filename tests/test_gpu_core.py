@@ -1126,12 +1126,12 @@ def test_batched_packs_equal_packs_of_one(W, layout):
 
 @pytest.mark.parametrize("layout", ["sell", "dense", "kept"])
 @pytest.mark.parametrize("n,count,checked", [(64, 17, (0, 9, 15, 16)), (64, 26, (3, 23, 24, 25)),
-                                             (256, 59, (0, 8, 55, 58)), (512, 9, (7, 8)), (512, 26, (3, 24, 25))])
+                                             (256, 59, (0, 8, 55, 58)), (512, 9, (7, 8)), (512, 11, (0, 10)),
+                                             (512, 26, (3, 24, 25))])
 def test_batched_packs_of_every_arrangement_keep_the_iterates(W, layout, n, count, checked):
     """Packs of an operator that take turns, the last of them of one, two or four
-    slots, and (9 problems of 512 x 512) a second pack by itself, with loads ahead and
-    planes and (59 of 256 x 256 and more on the tiles) without: a problem's
-    iterate is that of a batch of its own, to the last bit, and it stops at the same check."""
+    slots, and (9 and 11 problems of 512 x 512) a second pack by itself, with loads ahead
+    and planes and (26 of 512 x 512) without: a problem's iterate is that of a batch of its own, to the last bit, and it stops at the same check."""
     th = W.build_theta(synth.psf_rotating(n, 2.5, 1.0), "haar", 3, 12 * n * n + 5)
     th.lipschitz_lanczos()
     if layout == "sell":
