@@ -139,23 +139,24 @@ __global__ __launch_bounds__(kT * kT) void k_exact_reach(ExDev E, short2* __rest
   const int n = E.P.n, R = E.P.R, dy = blockIdx.y;
   const int64_t N = static_cast<int64_t>(n) * n;
   const int r = static_cast<int>(blockIdx.x) / E.ntile * kT + static_cast<int>(threadIdx.x) / kT;
-  const int c = static_cast<int>(blockIdx.x) % E.ntile * kT + static_cast<int>(threadIdx.x) % kT;
+  const int col = static_cast<int>(blockIdx.x) % E.ntile * kT + static_cast<int>(threadIdx.x) % kT;
   if (threadIdx.x == 0) {
     lo = R + 1;
     hi = -R - 1;
   }
   __syncthreads();
   int first = R + 1, last = -R - 1;
-  if (r < n && c < n) {
-    const int64_t s = static_cast<int64_t>(r) * n + c;
+  if (r < n && col < n) {
+    const int64_t s = static_cast<int64_t>(r) * n + col;
     const double k0 = E.coef[s], k1 = E.coef[N + s], k2 = E.coef[2 * N + s], k3 = E.coef[3 * N + s];
     const double fy = static_cast<double>(dy), R1 = static_cast<double>(R);
-    const double a = fma(k0, k0, k3 * k3), mid = -fy * (k0 * k1 - k3 * k2) / a;
-    const double half = sqrt(fmax((E.never - fy * fy * fma(k1, k1, k2 * k2)) / a + mid * mid, 0.0)) + 1.0;
-    // a not-a-number (squares that overflow, PSFs without weights): every offset is tried
-    const bool known = mid - half <= mid + half && a < 1e300;
-    int x0 = known ? static_cast<int>(fmax(floor(mid - half), -R1)) : -R;
-    int x1 = known ? static_cast<int>(fmin(ceil(mid + half), R1)) : R;
+    // q = a (dx - mid)^2 + (c dy^2 - a mid^2)
+    const double a = fma(k0, k0, k3 * k3), c = fma(k1, k1, k2 * k2), mid = -fy * (k0 * k1 - k3 * k2) / a;
+    const double half = sqrt(fmax((E.never - fy * fy * c) / a + mid * mid, 0.0)) + 1.0;
+    // squares that overflow, PSFs without weights (NaN): every offset is tried
+    const bool known = a < 1e300 && c < 1e300;
+    int x0 = known ? static_cast<int>(fmin(fmax(floor(mid - half), -R1), R1 + 1.0)) : -R;
+    int x1 = known ? static_cast<int>(fmax(fmin(ceil(mid + half), R1), -R1 - 1.0)) : R;
     while (x0 <= x1 && !(scaled_q(k0, k1, k2, k3, fy, static_cast<double>(x0)) <= E.never)) ++x0;
     while (x1 >= x0 && !(scaled_q(k0, k1, k2, k3, fy, static_cast<double>(x1)) <= E.never)) --x1;
     if (x0 <= x1) {

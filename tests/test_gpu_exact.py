@@ -195,3 +195,18 @@ def test_exact_fields_that_change_from_pixel_to_pixel(W, n, low, high, trunc):
     ex = W.Exact(field, "haar", 1)
     assert np.max(np.abs(host(ex.apply(dev(u))) - Hu)) <= 1e-7 * np.max(np.abs(Hu))
     assert np.max(np.abs(host(ex.apply(dev(u), adjoint=True)) - Hv)) <= 1e-7 * np.max(np.abs(Hv))
+
+
+@pytest.mark.parametrize("minor", [1e-140, 1e-160])
+def test_exact_lines_along_the_rows(W, minor):
+    """Axes so short that the coefficients' squares overflow, along the rows: each PSF
+    is a line of its row, and none of its offsets is missed."""
+    n = 32
+    full = lambda v: np.full(n * n, v)
+    major = np.random.default_rng(1).uniform(1.0, 4.0, n * n)
+    field = types.SimpleNamespace(n=n, sig_major=major, sig_minor=full(minor), angle=full(0.0), trunc=3.0)
+    u = np.random.default_rng(2).standard_normal(n * n).astype(np.float32)
+    Hu, Hv = direct_products(field, u, u)
+    ex = W.Exact(field, "haar", 1)
+    assert np.max(np.abs(host(ex.apply(dev(u))) - Hu)) <= 1e-7 * np.max(np.abs(Hu))
+    assert np.max(np.abs(host(ex.apply(dev(u), adjoint=True)) - Hv)) <= 1e-7 * np.max(np.abs(Hv))
